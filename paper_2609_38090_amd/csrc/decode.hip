@@ -220,163 +220,216 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_i4_kern
 
 // ---------------------------------------------------------------------------
 // Down projection + weighted combine.  Workgroup = 16 output rows c; its KS
-// waves split the R dimension.  For every non-empty expert, y = Qd H' with
-// per-64-row exponents of H', multiplied by the combine weight of each
-// (token, expert) pair and summed per token in a fixed order (expert list
-// order inside a wave, then wave order), so the result is deterministic.
-// H' has HD digits per entry (h_digits): an operand of 16 columns holds 5
-// tokens of three digits or 8 of two (column r16 = token r16/HD of the
-// group, digit r16%HD), and NG groups cover that many tokens per group.
+// waves split the k-steps (64 entries of R each) of the non-empty experts.
+// For every expert, y = Qd H' with per-64-row exponents of H', multiplied by
+// the combine weight of each (token, expert) pair and summed per token in a
+// fixed order (expert list order inside a wave, then wave order), so the
+// result is deterministic.  H' has HD digits per entry (h_digits): an operand
+// of 16 columns holds 5 tokens of three digits or 8 of two (column r16 = token
+// r16/HD of the group, digit r16%HD), and NG groups cover that many tokens.
 // ---------------------------------------------------------------------------
-template <int NG, int KS, bool I4, int HD, bool TE>
-__global__ __launch_bounds__(64 * KS) void decode_down_kernel(
-    int C, int R, int T, int max_active, ExpertPool ep, const DecodeWork* __restrict__ work,
-    const int8_t* __restrict__ hdig, const int32_t* __restrict__ hexp, float* __restrict__ out) {
+// One wave's k-steps [ks_beg, ks_end) of one expert (slot; positions off ..
+// off+n-1, descriptor wk), added into part[token][row] of the wave.
+template <int NG, bool I4, int HD, bool TE>
+__device__ __forceinline__ void down_steps(int C, int R, const ExpertPool& ep,
+                                           const DecodeWork& wk, int slot, int off, int n,
+                                           int ks_beg, int ks_end,
+                                           const int8_t* __restrict__ hdig,
+                                           const int32_t* __restrict__ hexp, float (*part)[16]) {
   constexpr int TPG = h_tok_per_group(HD);
-  __shared__ float part[KS][MIRA_DECODE_MAX_TOKENS][16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // each wave adds only into its own slice, so it clears only that slice and
-  // nothing waits before the stream starts
-  for (int i = lane; i < MIRA_DECODE_MAX_TOKENS * 16; i += 64) (&part[wave][0][0])[i] = 0.f;
-
   static_assert(!TE || (NG == 1 && HD == 3), "per-tile exponents: one token, three digits");
+  const int lane = threadIdx.x & 63;
   const int r16 = lane & 15, kg = lane >> 4;
   // TE: column r16 < 12 is digit d of the k-step's tile j = r16/3 (k group
   // j), so each tile's digits carry their own exponent; otherwise column
   // r16 is digit d of token m
   const int m = r16 / HD, d = r16 - HD * m;
   const int nks = R / 64;
-  // k-steps per wave; even for INT4, whose loads cover two k-steps
-  const int spw = I4 ? (((nks + KS - 1) / KS + 1) & ~1) : (nks + KS - 1) / KS;
-  const int ks_beg = wave * spw, ks_end = min(nks, ks_beg + spw);
+  // tile row c0/16 of the down matrix: INT8 tiles of 1 KB (lane l at 16*l),
+  // or INT4 nibble tiles of two groups (lane l at 16*l) and the tile-row's
+  // 32-byte scale blocks (lane l at 8*l of a 16-group run)
+  const int8_t* base = ep.pool + (size_t)slot * ep.stride;
+  const int8_t* dp = I4 ? base + 2 * i4_matrix_bytes(R, C) + (size_t)blockIdx.x * (nks / 2) * kI4PairTile +
+                              lane * 16
+                        : base + (size_t)2 * R * C + (size_t)blockIdx.x * nks * 1024 + lane * 16;
+  const int8_t* sp = base + 2 * i4_matrix_bytes(R, C) + i4_nib_bytes(C, R) +
+                     (size_t)blockIdx.x * nks * 32 + lane * 8;
+  const int8_t* bp[NG];
+  const int32_t* hx[NG];
+  bool bv[NG];
+#pragma unroll
+  for (int cg = 0; cg < NG; ++cg) {
+    const int i = TE ? 0 : cg * TPG + m;
+    bv[cg] = (TE ? r16 < 12 : r16 < HD * TPG) && i < n;
+    const size_t pos = (size_t)off + (bv[cg] ? i : 0);
+    bp[cg] = hdig + (pos * HD + d) * R + kg * 16;
+    hx[cg] = TE ? hexp + pos * (R / 16) + m : hexp + pos * nks;
+  }
+  // TE: only the lanes of k group j load their tile's digits
+  const bool bload = !TE || kg == m;
+  // the combine's token and weight, loaded ahead of the stream so that
+  // they return with the first batch
+  int ctok[NG];
+  float cwgt[NG];
+#pragma unroll
+  for (int cg = 0; cg < NG; ++cg) {
+    const bool lead = (TE ? r16 == 0 : d == 0) && bv[cg];
+    const int ti = TE ? 0 : cg * TPG + m;
+    ctok[cg] = lead ? wk.tok[ti] : 0;
+    cwgt[cg] = lead ? wk.w[ti] : 0.f;
+  }
+  float facc[NG][4];
+#pragma unroll
+  for (int cg = 0; cg < NG; ++cg)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) facc[cg][i] = 0.f;
 
-  for (int a = 0; a < max_active; ++a) {
-    const DecodeWork& wk = work[a];
-    if (wk.group < 0) break;
-    // the slot the gate/up kernel resolved from the table (-1 if invalid)
-    const int slot = wk.slot;
-    if (slot < 0 || slot >= ep.n_slots) continue;
-    const int off = wk.off, n = wk.n;
-    // tile row c0/16 of the down matrix: INT8 tiles of 1 KB (lane l at 16*l),
-    // or INT4 nibble tiles of two groups (lane l at 16*l) and the tile-row's
-    // 32-byte scale blocks (lane l at 8*l of a 16-group run)
-    const int8_t* base = ep.pool + (size_t)slot * ep.stride;
-    const int8_t* dp = I4 ? base + 2 * i4_matrix_bytes(R, C) + (size_t)blockIdx.x * (nks / 2) * kI4PairTile +
-                                lane * 16
-                          : base + (size_t)2 * R * C + (size_t)blockIdx.x * nks * 1024 + lane * 16;
-    const int8_t* sp = base + 2 * i4_matrix_bytes(R, C) + i4_nib_bytes(C, R) +
-                       (size_t)blockIdx.x * nks * 32 + lane * 8;
-    const int8_t* bp[NG];
-    const int32_t* hx[NG];
-    bool bv[NG];
+  // k-steps per batch: with 14 or 16 waves (up to four per SIMD, at most
+  // 128 registers each) half the batch of the 8-wave layout
+  constexpr int kDecUnroll = dec_unroll(NG) / 2;
+  static_assert(kDecUnroll % 2 == 0 && kDecUnroll <= 16, "INT4 batches cover whole tiles");
+  struct Batch {
+    v4i a[I4 ? kDecUnroll / 2 : kDecUnroll], b[kDecUnroll][NG];
+    uint2 s4;  // INT4: lane l holds group ks0 + l/4, rows 4*(l%4) .. +3
+    int he[kDecUnroll][NG];
+  };
+  auto issue = [&](Batch& bt, int ks0) {
+    if constexpr (I4) {
 #pragma unroll
-    for (int cg = 0; cg < NG; ++cg) {
-      const int i = TE ? 0 : cg * TPG + m;
-      bv[cg] = (TE ? r16 < 12 : r16 < HD * TPG) && i < n;
-      const size_t pos = (size_t)off + (bv[cg] ? i : 0);
-      bp[cg] = hdig + (pos * HD + d) * R + kg * 16;
-      hx[cg] = TE ? hexp + pos * (R / 16) + m : hexp + pos * nks;
+      for (int p = 0; p < kDecUnroll / 2; ++p) {
+        const bool in = ks0 + 2 * p < ks_end;
+        bt.a[p] = in ? ld16_stream(dp + (size_t)(ks0 / 2 + p) * kI4PairTile) : zero16();
+      }
+      const bool sin = (lane >> 2) < kDecUnroll && ks0 + (lane >> 2) < ks_end;
+      bt.s4 = sin ? ld8_stream(sp + (size_t)ks0 * 32) : uint2{0, 0};
     }
-    // TE: only the lanes of k group j load their tile's digits
-    const bool bload = !TE || kg == m;
-    // the combine's token and weight, loaded ahead of the stream so that
-    // they return with the first batch
-    int ctok[NG];
-    float cwgt[NG];
 #pragma unroll
-    for (int cg = 0; cg < NG; ++cg) {
-      const bool lead = (TE ? r16 == 0 : d == 0) && bv[cg];
-      const int ti = TE ? 0 : cg * TPG + m;
-      ctok[cg] = lead ? wk.tok[ti] : 0;
-      cwgt[cg] = lead ? wk.w[ti] : 0.f;
+    for (int u = 0; u < kDecUnroll; ++u) {
+      const int ks = ks0 + u;
+      const bool in = ks < ks_end;
+      if constexpr (!I4) bt.a[u] = in ? ld16_stream(dp + ks * 1024) : zero16();
+#pragma unroll
+      for (int cg = 0; cg < NG; ++cg) {
+        bt.b[u][cg] = (in && bv[cg] && bload) ? ld16(bp[cg] + ks * 64) : zero16();
+        bt.he[u][cg] = (in && bv[cg]) ? hx[cg][TE ? 4 * ks : ks] : 0;
+      }
     }
-    float facc[NG][4];
+  };
+  auto consume = [&](const Batch& bt) {
 #pragma unroll
-    for (int cg = 0; cg < NG; ++cg)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) facc[cg][i] = 0.f;
-
-    // k-steps per batch: with 14 or 16 waves (up to four per SIMD, at most
-    // 128 registers each) half the batch of the 8-wave layout
-    static_assert(KS > 8, "the batch size assumes more than 8 waves");
-    constexpr int kDecUnroll = dec_unroll(NG) / 2;
-    static_assert(kDecUnroll % 2 == 0 && kDecUnroll <= 16, "INT4 batches cover whole tiles");
-    struct Batch {
-      v4i a[I4 ? kDecUnroll / 2 : kDecUnroll], b[kDecUnroll][NG];
-      uint2 s4;  // INT4: lane l holds group ks0 + l/4, rows 4*(l%4) .. +3
-      int he[kDecUnroll][NG];
-    };
-    auto issue = [&](Batch& bt, int ks0) {
+    for (int u = 0; u < kDecUnroll; ++u) {
+      v4i a;
+      float s4[4] = {1.f, 1.f, 1.f, 1.f};
       if constexpr (I4) {
-#pragma unroll
-        for (int p = 0; p < kDecUnroll / 2; ++p) {
-          const bool in = ks0 + 2 * p < ks_end;
-          bt.a[p] = in ? ld16_stream(dp + (size_t)(ks0 / 2 + p) * kI4PairTile) : zero16();
-        }
-        const bool sin = (lane >> 2) < kDecUnroll && ks0 + (lane >> 2) < ks_end;
-        bt.s4 = sin ? ld8_stream(sp + (size_t)ks0 * 32) : uint2{0, 0};
+        const v4i q2 = bt.a[u / 2];
+        a = (u & 1) ? i4_operand(uint2{(uint32_t)q2[2], (uint32_t)q2[3]})
+                    : i4_operand(uint2{(uint32_t)q2[0], (uint32_t)q2[1]});
+        i4_scales(uint2{(uint32_t)__shfl((int)bt.s4.x, 4 * u + kg, 64),
+                        (uint32_t)__shfl((int)bt.s4.y, 4 * u + kg, 64)}, s4);
+      } else {
+        a = bt.a[u];
       }
 #pragma unroll
-      for (int u = 0; u < kDecUnroll; ++u) {
-        const int ks = ks0 + u;
-        const bool in = ks < ks_end;
-        if constexpr (!I4) bt.a[u] = in ? ld16_stream(dp + ks * 1024) : zero16();
+      for (int cg = 0; cg < NG; ++cg) {
+        const v4i sres = mfma_i8(a, bt.b[u][cg], zero16());
+        // digit weight and H' exponent; INT4 adds the row scales and 1/16
+        const float sc = bv[cg] ? ldexpf(1.f, 8 * d - bt.he[u][cg] - (I4 ? 4 : 0)) : 0.f;
 #pragma unroll
-        for (int cg = 0; cg < NG; ++cg) {
-          bt.b[u][cg] = (in && bv[cg] && bload) ? ld16(bp[cg] + ks * 64) : zero16();
-          bt.he[u][cg] = (in && bv[cg]) ? hx[cg][TE ? 4 * ks : ks] : 0;
-        }
+        for (int i = 0; i < 4; ++i) facc[cg][i] = fmaf((float)sres[i], sc * s4[i], facc[cg][i]);
       }
-    };
-    auto consume = [&](const Batch& bt) {
-#pragma unroll
-      for (int u = 0; u < kDecUnroll; ++u) {
-        v4i a;
-        float s4[4] = {1.f, 1.f, 1.f, 1.f};
-        if constexpr (I4) {
-          const v4i q2 = bt.a[u / 2];
-          a = (u & 1) ? i4_operand(uint2{(uint32_t)q2[2], (uint32_t)q2[3]})
-                      : i4_operand(uint2{(uint32_t)q2[0], (uint32_t)q2[1]});
-          i4_scales(uint2{(uint32_t)__shfl((int)bt.s4.x, 4 * u + kg, 64),
-                          (uint32_t)__shfl((int)bt.s4.y, 4 * u + kg, 64)}, s4);
-        } else {
-          a = bt.a[u];
-        }
-#pragma unroll
-        for (int cg = 0; cg < NG; ++cg) {
-          const v4i sres = mfma_i8(a, bt.b[u][cg], zero16());
-          // digit weight and H' exponent; INT4 adds the row scales and 1/16
-          const float sc = bv[cg] ? ldexpf(1.f, 8 * d - bt.he[u][cg] - (I4 ? 4 : 0)) : 0.f;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) facc[cg][i] = fmaf((float)sres[i], sc * s4[i], facc[cg][i]);
-        }
-      }
-    };
-    // one batch per iteration (see the gate/up body)
-    for (int ks = ks_beg; ks < ks_end; ks += kDecUnroll) {
-      Batch bt;
-      issue(bt, ks);
-      consume(bt);
     }
+  };
+  // one batch per iteration (see the gate/up body)
+  for (int ks = ks_beg; ks < ks_end; ks += kDecUnroll) {
+    Batch bt;
+    issue(bt, ks);
+    consume(bt);
+  }
 #pragma unroll
-    for (int cg = 0; cg < NG; ++cg) {
-      const bool lead = (TE ? r16 == 0 : d == 0) && bv[cg];
+  for (int cg = 0; cg < NG; ++cg) {
+    const bool lead = (TE ? r16 == 0 : d == 0) && bv[cg];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float v;
-        if constexpr (TE) {
-          // the twelve (tile, digit) columns of the row (lanes 12-15 hold 0)
-          v = facc[cg][i];
-          v += __shfl_xor(v, 1, 64);
-          v += __shfl_xor(v, 2, 64);
-          v += __shfl_xor(v, 4, 64);
-          v += __shfl_xor(v, 8, 64);
-        } else {
-          v = facc[cg][i] + __shfl_down(facc[cg][i], 1, 64);
-          if constexpr (HD == 3) v += __shfl_down(facc[cg][i], 2, 64);
-        }
-        if (lead) part[wave][ctok[cg]][kg * 4 + i] += cwgt[cg] * v;
+    for (int i = 0; i < 4; ++i) {
+      float v;
+      if constexpr (TE) {
+        // the twelve (tile, digit) columns of the row (lanes 12-15 hold 0)
+        v = facc[cg][i];
+        v += __shfl_xor(v, 1, 64);
+        v += __shfl_xor(v, 2, 64);
+        v += __shfl_xor(v, 4, 64);
+        v += __shfl_xor(v, 8, 64);
+      } else {
+        v = facc[cg][i] + __shfl_down(facc[cg][i], 1, 64);
+        if constexpr (HD == 3) v += __shfl_down(facc[cg][i], 2, 64);
       }
+      if (lead) part[ctok[cg]][kg * 4 + i] += cwgt[cg] * v;
+    }
+  }
+}
+
+// NGMAX token groups cover the call.  An expert of at most one group of
+// tokens runs the one-group body (batches twice as long) even if the call
+// needs two.  The waves split either every expert's k-steps (each wave a range
+// of each expert), or with FLAT the concatenated k-steps of all experts, so
+// that a wave streams long runs of one to a few experts (kDownFlatSteps).
+template <int NGMAX, int KS, bool I4, int HD, bool TE, bool FLAT>
+__global__ __launch_bounds__(64 * KS) void decode_down_kernel(
+    int C, int R, int T, int max_active, ExpertPool ep, const DecodeWork* __restrict__ work,
+    const int8_t* __restrict__ hdig, const int32_t* __restrict__ hexp, float* __restrict__ out) {
+  __shared__ float part[KS][MIRA_DECODE_MAX_TOKENS][16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // each wave adds only into its own slice, so it clears only that slice and
+  // nothing waits before the stream starts
+  for (int i = lane; i < MIRA_DECODE_MAX_TOKENS * 16; i += 64) (&part[wave][0][0])[i] = 0.f;
+  static_assert(KS > 8, "the batch size assumes more than 8 waves");
+
+  const int nks = R / 64;
+  auto steps = [&](const DecodeWork& wk, int slot, int off, int n, int ks_beg, int ks_end) {
+    if (NGMAX == 1 || n <= h_tok_per_group(HD))
+      down_steps<1, I4, HD, TE>(C, R, ep, wk, slot, off, n, ks_beg, ks_end, hdig, hexp, part[wave]);
+    else
+      down_steps<NGMAX, I4, HD, TE>(C, R, ep, wk, slot, off, n, ks_beg, ks_end, hdig, hexp, part[wave]);
+  };
+  if constexpr (FLAT) {
+    // non-empty experts: every descriptor up to max_active is written, the
+    // unused ones with group -1
+    int n_act = 0;
+    for (int b = 0; b < max_active; b += 64) {
+      const int a = b + lane;
+      n_act += __popcll(__ballot(a < max_active && work[a < max_active ? a : 0].group >= 0));
+    }
+    const int total = n_act * nks;
+    // even for INT4, whose loads cover two k-steps (nks is even there)
+    const int per = I4 ? (((total + KS - 1) / KS + 1) & ~1) : (total + KS - 1) / KS;
+    const int u0 = wave * per, u1 = min(total, u0 + per);
+    if (u0 < u1) {
+      int a = u0 / nks;
+      int slot = work[a].slot, off = work[a].off, n = work[a].n;
+      for (int u = u0; u < u1;) {
+        const int ks_beg = u - a * nks, ks_end = min(nks, u1 - a * nks);
+        // the next expert's header loads while this one streams
+        const int an = min(a + 1, n_act - 1);
+        const int slot_n = work[an].slot, off_n = work[an].off, n_n = work[an].n;
+        if (slot >= 0 && slot < ep.n_slots) steps(work[a], slot, off, n, ks_beg, ks_end);
+        u = a * nks + ks_end;
+        ++a;
+        slot = slot_n;
+        off = off_n;
+        n = n_n;
+      }
+    }
+  } else {
+    // k-steps per wave; even for INT4, whose loads cover two k-steps
+    const int spw = I4 ? (((nks + KS - 1) / KS + 1) & ~1) : (nks + KS - 1) / KS;
+    const int ks_beg = wave * spw, ks_end = min(nks, ks_beg + spw);
+    for (int a = 0; a < max_active; ++a) {
+      const DecodeWork& wk = work[a];
+      if (wk.group < 0) break;
+      // the slot the gate/up kernel resolved from the table (-1 if invalid)
+      const int slot = wk.slot;
+      if (slot < 0 || slot >= ep.n_slots) continue;
+      steps(wk, slot, wk.off, wk.n, ks_beg, ks_end);
     }
   }
   __syncthreads();
@@ -397,13 +450,26 @@ __global__ __launch_bounds__(64 * KS) void decode_down_kernel(
 template <bool I4>
 constexpr int down_waves() { return I4 ? 14 : 16; }
 
+// Most k-steps per expert (R/64) for which the waves split the concatenated
+// k-steps of all experts (FLAT) instead of each expert's.  Splitting each
+// expert leaves a wave one to two k-steps of it at R = 1408 and one memory
+// round trip per expert, up to T*k + S in a row; with FLAT a wave streams a
+// few long runs.  The fine-grained layer (C 2048, R 1408, 64 experts top-6, 2
+// shared), us per call with split experts / FLAT: 1 token 44.4 / 36.0, 8
+// tokens 81.9 / 67.7, 16 tokens INT4 131 / 99.  FLAT is even with or ahead of
+// split experts by up to 2% up to R = 5632 (88 k-steps); at R = 8192 it is
+// 1% ahead with 8 tokens and 2% behind with 16, and at 14336, where a split
+// expert fills two batches of a wave, 1% behind with one token.
+constexpr int kDownFlatSteps = 96;
+
 template <int NG, bool I4, int HD, bool TE = false>
 static void launch_decode_down_ng(const Layout& L, const WsPtr& w, const ExpertPool& ep,
                                   float* out, hipStream_t st) {
   constexpr int KS = down_waves<I4>();
-  launch_timed("decode_down", (decode_down_kernel<NG, KS, I4, HD, TE>), dim3(L.C / 16),
-               dim3(64 * KS), 0, st, L.C, L.R, L.T, decode_max_active(L), ep, w.dwork, w.hdig,
-               w.hexp, out);
+  const auto kern = L.R / 64 <= kDownFlatSteps ? decode_down_kernel<NG, KS, I4, HD, TE, true>
+                                               : decode_down_kernel<NG, KS, I4, HD, TE, false>;
+  launch_timed("decode_down", kern, dim3(L.C / 16), dim3(64 * KS), 0, st, L.C, L.R, L.T,
+               decode_max_active(L), ep, w.dwork, w.hdig, w.hexp, out);
 }
 
 template <int NG, bool I4>

@@ -1,0 +1,41 @@
+"""Decode calls at the edges of the expert kernels' work splits, against the
+oracle (run_and_check: routing bit-exact, every output row within the bars, and
+the decode floor).
+
+Down projection: up to 96 k-steps (64 entries of R) per expert the waves split
+the concatenated k-steps of all non-empty experts, above that each expert's;
+an expert of at most one token group runs the one-group body."""
+import pytest
+
+from gpu_layer import Layer, decode_rel_floor, run_and_check
+from mira_inputs import MoEConfig
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(cid, T, C, R, E, k, S=0, act="bf16"):
+    return MoEConfig(f"split_{cid}", cid, T=T, C=C, R=R, E=E, k=k, S=S, act=act, zipf_s=0.5)
+
+
+DOWN = [
+    # more than 64 non-empty experts (descriptors counted in two passes), some
+    # with one token and shared ones with 16
+    ("many_experts", _cfg(701, 16, 128, 128, 120, 8, S=2), "int8"),
+    ("many_experts_int4", _cfg(702, 16, 128, 256, 120, 8, S=1), "int4"),
+    # one k-step in all: 15 (13) waves without work
+    ("one_step", _cfg(703, 1, 64, 64, 1, 1), "int8"),
+    ("two_steps_int4", _cfg(704, 9, 128, 128, 1, 1), "int4"),
+    # the largest ffn with concatenated k-steps and the next one
+    ("last_flat", _cfg(705, 9, 64, 6144, 4, 2), "int8"),
+    ("first_split", _cfg(706, 9, 64, 6208, 4, 2), "int8"),
+    ("last_flat_one", _cfg(707, 1, 64, 6144, 4, 2), "int8"),
+    ("first_split_int4", _cfg(708, 6, 128, 6272, 4, 2), "int4"),
+    # runs that start and end inside experts
+    ("ragged_runs", _cfg(709, 5, 192, 832, 7, 3, S=1, act="f32"), "int8"),
+]
+
+
+@pytest.mark.parametrize("cfg,fmt", [pytest.param(c, f, id=i) for i, c, f in DOWN])
+def test_down_split(mira, cfg, fmt):
+    _, errs, _, _ = run_and_check(Layer(cfg, fmt=fmt))
+    assert errs[0] < decode_rel_floor(cfg.T), errs
