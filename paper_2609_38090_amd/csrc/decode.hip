@@ -28,32 +28,29 @@ namespace mira {
 // rows a read phase touches fall in distinct banks) and the loop reads them
 // from there.
 constexpr int kXlMaxC = 4096;
-constexpr int kXlUnroll = 16;  // k-steps per weight batch
+inline uint32_t xl_bytes(int C) { return 3 * kTokPerGroup * (C + 16); }
+// k-steps per weight batch: with the digits in LDS, 8 steps let three waves
+// share a SIMD; fine-grained layer, 4 / 16 tokens: 50.0 / 96.0 us per call
+// against 50.8 / 99.7 with 16 steps (and 50.0 / 95.4 with 6, which costs the
+// Mixtral shape 2%)
+constexpr int kXlUnroll = 8;
+// the same for an INT8 expert of one token group in a call of several: the
+// body shares its registers with the wider ones
+constexpr int kOneGroupUnroll = 8;
 // k-steps per weight batch of the one-token INT4 tile kernel (6 KB per wave):
 // a wave holds one tile and cannot issue its next loads while it unpacks and
 // scales a batch, and shorter batches measured faster than 4, 8 or 16 steps
 constexpr int kTileI4Unroll = 6;
 
-template <int NG, bool I4, bool XL>
-__device__ __forceinline__ void decode_gateup_body(int C, int R, const ExpertPool& ep,
-                                                   DecodeWork* __restrict__ work,
+// One (expert, row block) of a gate/up call for an expert of at most NG token
+// groups (wk, resolved slot), H' in HD digits.
+template <int NG, int NGMAX, int HD, bool I4, bool XL>
+__device__ __forceinline__ void decode_gateup_body(int C, int R, int rb, int slot,
+                                                   const ExpertPool& ep, const DecodeWork& wk,
                                                    const int8_t* __restrict__ xdig,
                                                    int8_t* __restrict__ hdig,
-                                                   int32_t* __restrict__ hexp) {
-  __shared__ float bmax[4][NG * kTokPerGroup];
-  const int nrb = R / kBlk;
-  const int a = blockIdx.x / nrb, rb = blockIdx.x - a * nrb;
-  const DecodeWork& wk = work[a];
-  const int g = wk.group;
-  if (g < 0) return;
-  const int slot = ep.slot_table[g];  // read now: the table may change after routing
-  const bool ok = slot >= 0 && slot < ep.n_slots;
-  // block 0 of the expert keeps the resolved slot for the down kernel
-  if (rb == 0 && threadIdx.x == 0) work[a].slot = ok ? slot : -1;
-  if (!ok) {
-    if (threadIdx.x == 0 && ep.status) atomicOr(ep.status, slot < 0 ? 1 : 2);
-    return;
-  }
+                                                   int32_t* __restrict__ hexp,
+                                                   float (*bmax)[kDecodeMaxGroups * kTokPerGroup]) {
   const int n = wk.n;
   const int lane = threadIdx.x & 63;
   const int r16 = lane & 15, kg = lane >> 4;
@@ -71,7 +68,7 @@ __device__ __forceinline__ void decode_gateup_body(int C, int R, const ExpertPoo
   }
   if constexpr (XL) {
     static_assert(NG == 1, "one token group in LDS");
-    __shared__ __attribute__((aligned(16))) int8_t xl[16 * (kXlMaxC + 16)];
+    extern __shared__ __attribute__((aligned(16))) int8_t xl[];  // xl_bytes(C)
     const int ld = C + 16;
     const int chunks = C / 16;
     // only the digit rows of the group's tokens are staged; lanes of the
@@ -91,36 +88,78 @@ __device__ __forceinline__ void decode_gateup_body(int C, int R, const ExpertPoo
 #pragma unroll
     for (int cg = 0; cg < NG; ++cg) xr[cg] = xl + (size_t)(cg * 16 + r16) * ld + kg * 16;
     const auto load_x = [&](int cg, int ks) { return bv[cg] ? *(const v4i*)(xr[cg] + ks * 64) : zero16(); };
-    gateup_block_i4<NG, kXlUnroll, true>(C, R, rb, (const uint8_t*)ep.pool + (size_t)slot * ep.stride,
-                                         wk.off, bv, xev, load_x, hdig, hexp, bmax);
+    gateup_block_i4<NG, HD, kXlUnroll, true>(C, R, rb, (const uint8_t*)ep.pool + (size_t)slot * ep.stride,
+                                             wk.off, bv, xev, load_x, hdig, hexp, bmax);
     return;
   }
   const auto load_b = [&](int cg, int ks) { return ld16(bp[cg] + ks * 64); };
   if constexpr (I4)
-    gateup_block_i4<NG, dec_unroll(NG), false>(C, R, rb,
-                                               (const uint8_t*)ep.pool + (size_t)slot * ep.stride,
-                                               wk.off, bv, xev, load_b, hdig, hexp, bmax);
+    gateup_block_i4<NG, HD, dec_unroll(NG), false>(C, R, rb,
+                                                   (const uint8_t*)ep.pool + (size_t)slot * ep.stride,
+                                                   wk.off, bv, xev, load_b, hdig, hexp, bmax);
   else
-    gateup_block<NG>(C, R, rb, ep.pool + (size_t)slot * ep.stride, wk.off, bv, xev, load_b, hdig,
-                     hexp, bmax);
+    gateup_block<NG, HD, (NGMAX > 1 && NG == 1) ? kOneGroupUnroll : dec_unroll(NG)>(C, R, rb, ep.pool + (size_t)slot * ep.stride, wk.off, bv, xev, load_b, hdig,
+                         hexp, bmax);
 }
 
-template <int NG, bool I4>
+// Workgroup = (non-empty expert, 64-row block) of a call that NGMAX token
+// groups cover; the expert's own token count chooses the body (most experts
+// of a call hold a few of its tokens, and a body for fewer groups spends
+// fewer matrix-core steps and holds longer weight batches).  INT4, whose loop
+// is not a pure stream, gains most: Mixtral shape, 12 / 16 tokens, 199 / 238
+// -> 184 / 210 us per call.  INT8 is bound by the stream: 8 / 12 tokens
+// 194.7 / 244.7 -> 192.6 / 238.7 us, and at four groups the narrow bodies are
+// no faster (262.5 / 263.4) and the fine-grained layer 2% slower, so that call
+// keeps one body.
+template <int NGMAX, bool I4, bool XL>
+__device__ __forceinline__ void decode_gateup_groups(int C, int R, const ExpertPool& ep,
+                                                     DecodeWork* __restrict__ work,
+                                                     const int8_t* __restrict__ xdig,
+                                                     int8_t* __restrict__ hdig,
+                                                     int32_t* __restrict__ hexp) {
+  constexpr int HD = h_digits(NGMAX);
+  __shared__ float bmax[4][kDecodeMaxGroups * kTokPerGroup];
+  const int nrb = R / kBlk;
+  const int a = blockIdx.x / nrb, rb = blockIdx.x - a * nrb;
+  const DecodeWork& wk = work[a];
+  const int g = wk.group;
+  if (g < 0) return;
+  const int slot = ep.slot_table[g];  // read now: the table may change after routing
+  const bool ok = slot >= 0 && slot < ep.n_slots;
+  // block 0 of the expert keeps the resolved slot for the down kernel
+  if (rb == 0 && threadIdx.x == 0) work[a].slot = ok ? slot : -1;
+  if (!ok) {
+    if (threadIdx.x == 0 && ep.status) atomicOr(ep.status, slot < 0 ? 1 : 2);
+    return;
+  }
+  const int n = wk.n;
+  constexpr bool by_count = NGMAX > 1 && (I4 || NGMAX < 4);
+  if (NGMAX == 1 || (by_count && n <= kTokPerGroup))
+    decode_gateup_body<1, NGMAX, HD, I4, XL>(C, R, rb, slot, ep, wk, xdig, hdig, hexp, bmax);
+  else if (NGMAX == 2 || (by_count && n <= 2 * kTokPerGroup))
+    decode_gateup_body<NGMAX < 2 ? NGMAX : 2, NGMAX, HD, I4, false>(C, R, rb, slot, ep, wk, xdig, hdig, hexp, bmax);
+  else
+    decode_gateup_body<NGMAX, NGMAX, HD, I4, false>(C, R, rb, slot, ep, wk, xdig, hdig, hexp, bmax);
+}
+
+template <int NGMAX, bool I4>
 __global__ __launch_bounds__(256) void decode_gateup_kernel(int C, int R, ExpertPool ep,
                                                             DecodeWork* __restrict__ work,
                                                             const int8_t* __restrict__ xdig,
                                                             int8_t* __restrict__ hdig,
                                                             int32_t* __restrict__ hexp) {
-  decode_gateup_body<NG, I4, false>(C, R, ep, work, xdig, hdig, hexp);
+  decode_gateup_groups<NGMAX, I4, false>(C, R, ep, work, xdig, hdig, hexp);
 }
 
-// The LDS variant keeps two workgroups per CU (the 64 KB of digits each).
+// The INT4 variant with the digits of one-group experts in LDS: at most
+// 62 KB (C = 4096), so that two or more workgroups share a CU.
+template <int NGMAX>
 __global__ __launch_bounds__(256, 2) void decode_gateup_xl_kernel(int C, int R, ExpertPool ep,
                                                                  DecodeWork* __restrict__ work,
                                                                  const int8_t* __restrict__ xdig,
                                                                  int8_t* __restrict__ hdig,
                                                                  int32_t* __restrict__ hexp) {
-  decode_gateup_body<1, true, true>(C, R, ep, work, xdig, hdig, hexp);
+  decode_gateup_groups<NGMAX, true, true>(C, R, ep, work, xdig, hdig, hexp);
 }
 
 // One-token calls: every wave streams one 16-row tile of the concatenated
@@ -162,7 +201,7 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_kernel(
   v4i accg[1], accu[1];
   float sg[4];
   const bool bva[1] = {bv};
-  gateup_tile_stream<1>(C, R, rt, ep.pool + (size_t)slot * ep.stride, bva, load_b, accg, accu, sg);
+  gateup_tile_stream<1, dec_unroll(1)>(C, R, rt, ep.pool + (size_t)slot * ep.stride, bva, load_b, accg, accu, sg);
   h_tile_1tok(R, rt, wk.off, bv, xe, accg[0], accu[0], sg, hdig, hexp);
 }
 
@@ -477,9 +516,10 @@ static void launch_decode_gateup(const Layout& L, const WsPtr& w, const ExpertPo
                                  hipStream_t st) {
   const int nrb = L.R / kBlk;
   const int max_active = decode_max_active(L);
-  if constexpr (I4 && NG == 1) {
+  if constexpr (I4) {
     if (L.C <= kXlMaxC) {
-      launch_timed("decode_gateup", decode_gateup_xl_kernel, dim3(max_active * nrb), dim3(256), 0, st,
+      launch_timed("decode_gateup", decode_gateup_xl_kernel<NG>, dim3(max_active * nrb), dim3(256),
+                   xl_bytes(L.C), st,
                    L.C, L.R, ep, w.dwork, w.xdig, w.hdig, w.hexp);
       return;
     }

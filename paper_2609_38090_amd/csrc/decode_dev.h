@@ -36,13 +36,12 @@ __host__ __device__ constexpr int dec_unroll(int ng) { return ng == 1 ? 16 : ng 
 // With HD = 3 digits H' has kFixBits bits against the block maximum, with
 // HD = 2 kHFixBits2; balanced base-256 digits hdig[(pos*HD + d)*R + r] and
 // the exponent hexp[pos*(R/64) + rb].
-template <int NG>
+template <int NG, int HD>
 __device__ __forceinline__ void write_h_digits(int R, int rb, int off, bool lead,
                                                const bool (&bv)[NG], const float (&hv)[NG][4],
                                                int8_t* __restrict__ hdig,
                                                int32_t* __restrict__ hexp,
-                                               float (*bmax)[NG * kTokPerGroup]) {
-  constexpr int HD = h_digits(NG);
+                                               float (*bmax)[kDecodeMaxGroups * kTokPerGroup]) {
   const int nrb = R / kBlk;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kg = lane >> 4;
@@ -89,7 +88,7 @@ __device__ __forceinline__ void write_h_digits(int R, int rb, int off, bool lead
 // (k = 64*ks + 16*(lane/16) .. +15).  On return accg/accu hold the int32
 // digit sums of rows 16*rtile + 4*(lane/16) + i (i < 4) for column r16, and
 // sg those rows' scales sigma_r.
-template <int NG, typename LoadB>
+template <int NG, int U, typename LoadB>
 __device__ __forceinline__ void gateup_tile_stream(int C, int R, int rtile,
                                                    const int8_t* __restrict__ blob,
                                                    const bool (&bv)[NG], LoadB load_b,
@@ -108,7 +107,7 @@ __device__ __forceinline__ void gateup_tile_stream(int C, int R, int rtile,
 #pragma unroll
   for (int cg = 0; cg < NG; ++cg) accg[cg] = accu[cg] = zero16();
 
-  constexpr int kDecUnroll = dec_unroll(NG);
+  constexpr int kDecUnroll = U;
   const int nks = C / 64;
   struct Batch {
     v4i ag[kDecUnroll], au[kDecUnroll], b[kDecUnroll][NG];
@@ -162,18 +161,18 @@ __device__ __forceinline__ float swiglu_h(int gsum_digits, int usum_digits, floa
 // +15, streamed by gateup_tile_stream); xev[cg] is the token's fixed-point
 // exponent.  Writes H' of the group's positions off .. off+n-1 as per-block
 // fixed-point digits (write_h_digits).
-template <int NG, typename LoadB>
+template <int NG, int HD, int U, typename LoadB>
 __device__ __forceinline__ void gateup_block(int C, int R, int rb, const int8_t* __restrict__ blob,
                                              int off, const bool (&bv)[NG], const int (&xev)[NG],
                                              LoadB load_b, int8_t* __restrict__ hdig,
                                              int32_t* __restrict__ hexp,
-                                             float (*bmax)[NG * kTokPerGroup]) {
+                                             float (*bmax)[kDecodeMaxGroups * kTokPerGroup]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kg = lane >> 4;
   const int m = r16 / 3, d = r16 - 3 * m;
   v4i accg[NG], accu[NG];
   float sg[4];
-  gateup_tile_stream<NG>(C, R, rb * (kBlk / 16) + wave, blob, bv, load_b, accg, accu, sg);
+  gateup_tile_stream<NG, U>(C, R, rb * (kBlk / 16) + wave, blob, bv, load_b, accg, accu, sg);
 
   const bool lead = d == 0;
   float hv[NG][4];
@@ -191,7 +190,7 @@ __device__ __forceinline__ void gateup_block(int C, int R, int rb, const int8_t*
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (kg == 0 && lead && r16 < 3 * kTokPerGroup) bmax[wave][cg * kTokPerGroup + m] = mx;
   }
-  write_h_digits<NG>(R, rb, off, lead, bv, hv, hdig, hexp, bmax);
+  write_h_digits<NG, HD>(R, rb, off, lead, bv, hv, hdig, hexp, bmax);
 }
 
 // One-token groups: writes H' of one 16-row tile (rows 16*rt .. +15) with
@@ -382,12 +381,12 @@ __device__ __forceinline__ void gateup_tile_stream_i4(int C, int R, int rtile,
 // work split, operands and output as gateup_block; each wave streams its
 // tile with gateup_tile_stream_i4, and H' = silu(G) (.) U (no shared scale to
 // fold).
-template <int NG, int U, bool B_AT_USE, typename LoadB>
+template <int NG, int HD, int U, bool B_AT_USE, typename LoadB>
 __device__ __forceinline__ void gateup_block_i4(int C, int R, int rb, const uint8_t* __restrict__ blob,
                                                 int off, const bool (&bv)[NG], const int (&xev)[NG],
                                                 LoadB load_b, int8_t* __restrict__ hdig,
                                                 int32_t* __restrict__ hexp,
-                                                float (*bmax)[NG * kTokPerGroup]) {
+                                                float (*bmax)[kDecodeMaxGroups * kTokPerGroup]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kg = lane >> 4;
   const int m = r16 / 3, d = r16 - 3 * m;
@@ -413,7 +412,7 @@ __device__ __forceinline__ void gateup_block_i4(int C, int R, int rb, const uint
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (kg == 0 && lead && r16 < 3 * kTokPerGroup) bmax[wave][cg * kTokPerGroup + m] = mx;
   }
-  write_h_digits<NG>(R, rb, off, lead, bv, hv, hdig, hexp, bmax);
+  write_h_digits<NG, HD>(R, rb, off, lead, bv, hv, hdig, hexp, bmax);
 }
 
 }  // namespace mira

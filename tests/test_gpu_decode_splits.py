@@ -4,7 +4,11 @@ the decode floor).
 
 Down projection: up to 96 k-steps (64 entries of R) per expert the waves split
 the concatenated k-steps of all non-empty experts, above that each expert's;
-an expert of at most one token group runs the one-group body."""
+an expert of at most one token group runs the one-group body.
+
+Gate/up: an expert's own token count (1 to 5, to 10, above) chooses the body
+in a call of several groups (INT8 up to 15 tokens, INT4 always); INT4 keeps the
+digits of one-group experts in LDS up to hidden 4096."""
 import pytest
 
 from gpu_layer import Layer, decode_rel_floor, run_and_check
@@ -37,5 +41,27 @@ DOWN = [
 
 @pytest.mark.parametrize("cfg,fmt", [pytest.param(c, f, id=i) for i, c, f in DOWN])
 def test_down_split(mira, cfg, fmt):
+    _, errs, _, _ = run_and_check(Layer(cfg, fmt=fmt))
+    assert errs[0] < decode_rel_floor(cfg.T), errs
+
+
+GATEUP = [
+    # every group size from 1 to T in one call: shared experts with T tokens,
+    # popular and rare routed ones
+    ("t10", _cfg(721, 10, 192, 128, 24, 3, S=1), "int8"),
+    ("t11", _cfg(722, 11, 192, 192, 6, 2, S=1), "int8"),
+    ("t15", _cfg(723, 15, 192, 192, 12, 4, S=1), "int8"),
+    ("t16", _cfg(724, 16, 192, 192, 12, 4, S=1), "int8"),
+    ("t10_int4", _cfg(725, 10, 256, 128, 24, 3, S=1), "int4"),
+    ("t16_int4", _cfg(726, 16, 384, 256, 12, 4, S=1), "int4"),
+    ("t6_int4_f32", _cfg(727, 6, 128, 128, 12, 2, act="f32"), "int4"),
+    # the largest hidden size with digits in LDS and the next one
+    ("lds_last", _cfg(728, 7, 4096, 128, 5, 2), "int4"),
+    ("lds_none", _cfg(729, 16, 4224, 128, 5, 2), "int4"),
+]
+
+
+@pytest.mark.parametrize("cfg,fmt", [pytest.param(c, f, id=i) for i, c, f in GATEUP])
+def test_gateup_groups(mira, cfg, fmt):
     _, errs, _, _ = run_and_check(Layer(cfg, fmt=fmt))
     assert errs[0] < decode_rel_floor(cfg.T), errs
