@@ -15,6 +15,7 @@
 // shared scale sigma_r factors out (section IV-B), y = Qd H' with
 // H' = sigma (.) silu(G) (.) U.
 #include "decode_dev.h"
+#include "route_dev.h"
 
 namespace mira {
 
@@ -169,31 +170,129 @@ __global__ __launch_bounds__(256, 2) void decode_gateup_xl_kernel(int C, int R, 
 // waves per workgroup, about one workgroup per CU).  The wave of tile 0 of
 // each expert also stores the slot it resolved from the table in the
 // expert's descriptor (-1 if invalid), for the down kernel.
+//
+// With SEL (the whole layer in one call, E <= 64) no selection kernel runs
+// between the router logits and this one: every wave selects from the logits
+// itself (one expert per lane, as decode_work_one_token), the waves of tile 0
+// write the descriptors and the last wave of the grid, which a ragged split
+// leaves idle, the optional outputs.  The selection replaces the load of a
+// descriptor and costs this kernel 0.3 us (8 experts) to 1.5 us (64 experts
+// top-6), a selection kernel 5.5 us and a boundary: 31.4 -> 27.1 us per call of
+// the fine-grained layer, 64.9 -> 64.8 us of Mixtral's (whose preparation was
+// one launch already).
 constexpr int kTileMaxWaves = 8;
 
-__global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_kernel(
-    int C, int R, int W, int ntiles, ExpertPool ep, DecodeWork* __restrict__ work,
-    const int8_t* __restrict__ xdig, int8_t* __restrict__ hdig, int32_t* __restrict__ hexp) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = blockIdx.x * W + wave;
-  if (wave >= W || t >= ntiles) return;
-  const int tpe = R / 16;
-  const int a = t / tpe, rt = t - a * tpe;
-  const DecodeWork& wk = work[a];
-  const int g = wk.group;
-  if (g < 0) return;
-  const int slot = ep.slot_table[g];  // read now: the table may change after routing
-  const bool ok = slot >= 0 && slot < ep.n_slots;
-  if (rt == 0 && lane == 0) work[a].slot = ok ? slot : -1;
-  if (!ok) {
-    if (lane == 0 && ep.status) atomicOr(ep.status, slot < 0 ? 1 : 2);
-    return;
+// What a SEL kernel selects from, and the optional outputs.
+struct OneTokenSel {
+  const float* logits;  // [E]
+  const int32_t* xe;    // the token's fixed-point exponent
+  int E, k, S, softmax_all;
+  PermOut o;
+};
+
+// The expert and slot of a wave's tile.
+struct TileExpert {
+  int slot;    // -1 if invalid
+  int off, xe; // permuted position; fixed-point exponent
+  bool any;    // the expert has the token
+};
+
+template <bool SEL>
+__device__ __forceinline__ bool tile_expert(int a, bool first, bool outputs, const ExpertPool& ep,
+                                            DecodeWork* __restrict__ work, const OneTokenSel& q,
+                                            TileExpert& te) {
+  const int lane = threadIdx.x & 63;
+  if constexpr (!SEL) {
+    const DecodeWork& wk = work[a];
+    const int g = wk.group;
+    if (g < 0) return false;
+    const int slot = ep.slot_table[g];  // read now: the table may change after routing
+    const bool ok = slot >= 0 && slot < ep.n_slots;
+    if (first && lane == 0) work[a].slot = ok ? slot : -1;
+    if (!ok) {
+      if (lane == 0 && ep.status) atomicOr(ep.status, slot < 0 ? 1 : 2);
+      return false;
+    }
+    te = TileExpert{slot, wk.off, wk.xe[0], wk.n > 0};
+    return true;
+  } else {
+    const int E = q.E, k = q.k, S = q.S;
+    const int slot_r = lane < E ? ep.slot_table[lane] : 0;
+    const int slot_s = lane < S ? ep.slot_table[E + lane] : 0;
+    const int xe = *q.xe;
+    bool sel;
+    int rank;
+    float w;
+    topk_lane64(q.logits, E, k, q.softmax_all, sel, rank, w);
+    const uint64_t mask = __ballot(sel);
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    const int at = __popcll(mask & lt);  // position among the selected experts
+    if (outputs) {
+      const PermOut& o = q.o;
+      if (sel) {
+        if (o.idx_out) o.idx_out[rank] = lane;
+        if (o.w_out) o.w_out[rank] = w;
+        if (o.order_out) o.order_out[at] = rank;
+      }
+      if (lane < E) {
+        if (o.counts_out) o.counts_out[lane] = sel ? 1 : 0;
+        if (o.offsets_out) o.offsets_out[lane] = at;
+      }
+      if (lane < S) {
+        if (o.order_out) o.order_out[k + lane] = k + lane;
+        if (o.counts_out) o.counts_out[E + lane] = 1;
+        if (o.offsets_out) o.offsets_out[E + lane] = k + lane;
+      }
+      if (lane == 0 && o.offsets_out) o.offsets_out[E + S] = k + S;
+      const bool lo = (sel && slot_r < 0) || (lane < S && slot_s < 0);
+      const bool hi = (sel && slot_r >= ep.n_slots) || (lane < S && slot_s >= ep.n_slots);
+      const int st = (__ballot(lo) ? 1 : 0) | (__ballot(hi) ? 2 : 0);
+      if (lane == 0 && ep.status) *ep.status = st;
+    }
+    if (a < 0) return false;
+    // group a: the a-th selected expert, then the shared ones
+    int g, slot;
+    float wa = 1.f;
+    if (a < k) {
+      g = __builtin_ctzll(__ballot(sel && at == a));
+      slot = __builtin_amdgcn_readlane(slot_r, g);
+      wa = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), g));
+    } else {
+      g = E + a - k;
+      slot = __builtin_amdgcn_readlane(slot_s, a - k);
+    }
+    const bool ok = slot >= 0 && slot < ep.n_slots;
+    if (first && lane == 0) {
+      DecodeWork* wk = work + a;
+      wk->group = g;
+      wk->slot = ok ? slot : -1;
+      wk->off = a;
+      wk->n = 1;
+      wk->tok[0] = 0;
+      wk->xe[0] = xe;
+      wk->w[0] = wa;
+    }
+    te = TileExpert{slot, a, xe, true};
+    return ok;
   }
+}
+
+template <bool SEL>
+__global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_kernel(
+    int C, int R, int W, int ntiles, ExpertPool ep, DecodeWork* __restrict__ work, OneTokenSel q,
+    const int8_t* __restrict__ xdig, int8_t* __restrict__ hdig, int32_t* __restrict__ hexp) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = blockIdx.x * W + wave;
+  const bool outputs = SEL && blockIdx.x == gridDim.x - 1 && wave == W - 1;
+  if (wave >= W || (t >= ntiles && !outputs)) return;
+  const int tpe = R / 16;
+  const int a = t < ntiles ? t / tpe : -1, rt = t - a * tpe;
+  TileExpert te;
+  if (!tile_expert<SEL>(a, rt == 0, outputs, ep, work, q, te)) return;
   const int r16 = lane & 15, kg = lane >> 4;
-  const bool bv = r16 < 3 && wk.n > 0;
-  const int tok = bv ? wk.tok[0] : 0;
-  const int xe = bv ? wk.xe[0] : 0;
-  const int8_t* bp = xdig + ((size_t)tok * kDigits + (bv ? r16 : 0)) * C + kg * 16;
+  const bool bv = r16 < 3 && te.any;
+  // a one-token call's only token is token 0
+  const int8_t* bp = xdig + (size_t)(bv ? r16 : 0) * C + kg * 16;
   const auto load_b = [&](int, int ks) { return ld16(bp + ks * 64); };
   // seven 16-row tiles per CU at Mixtral's shape: one wave per tile beat two
   // waves per tile (gate and up streamed apart, up sums handed over in LDS)
@@ -201,19 +300,21 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_kernel(
   v4i accg[1], accu[1];
   float sg[4];
   const bool bva[1] = {bv};
-  gateup_tile_stream<1, dec_unroll(1)>(C, R, rt, ep.pool + (size_t)slot * ep.stride, bva, load_b, accg, accu, sg);
-  h_tile_1tok(R, rt, wk.off, bv, xe, accg[0], accu[0], sg, hdig, hexp);
+  gateup_tile_stream<1, dec_unroll(1)>(C, R, rt, ep.pool + (size_t)te.slot * ep.stride, bva, load_b, accg,
+                                       accu, sg);
+  h_tile_1tok(R, rt, te.off, bv, te.xe, accg[0], accu[0], sg, hdig, hexp);
 }
 
 // One-token INT4 calls (C <= kXlMaxC): the same tile split, with the
 // token's three digit rows copied into LDS once per workgroup (row stride
 // C + 16 bytes), so a wave's batches hold only weight registers.  A one-token
 // call's only token is token 0, whatever expert a tile belongs to.
+template <bool SEL>
 __global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_i4_kernel(
-    int C, int R, int W, int ntiles, ExpertPool ep, DecodeWork* __restrict__ work,
+    int C, int R, int W, int ntiles, ExpertPool ep, DecodeWork* __restrict__ work, OneTokenSel q,
     const int8_t* __restrict__ xdig, int8_t* __restrict__ hdig, int32_t* __restrict__ hexp) {
   __shared__ __attribute__((aligned(16))) int8_t xl[kDigits * (kXlMaxC + 16)];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ld = C + 16, chunks = C / 16;
   for (int i = threadIdx.x; i < kDigits * chunks; i += blockDim.x) {
     const int row = i / chunks, c16 = i - row * chunks;
@@ -221,27 +322,20 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_i4_kern
   }
   __syncthreads();
   const int t = blockIdx.x * W + wave;
-  if (wave >= W || t >= ntiles) return;
+  const bool outputs = SEL && blockIdx.x == gridDim.x - 1 && wave == W - 1;
+  if (wave >= W || (t >= ntiles && !outputs)) return;
   const int tpe = R / 16;
-  const int a = t / tpe, rt = t - a * tpe;
-  const DecodeWork& wk = work[a];
-  const int g = wk.group;
-  if (g < 0) return;
-  const int slot = ep.slot_table[g];  // read now: the table may change after routing
-  const bool ok = slot >= 0 && slot < ep.n_slots;
-  if (rt == 0 && lane == 0) work[a].slot = ok ? slot : -1;
-  if (!ok) {
-    if (lane == 0 && ep.status) atomicOr(ep.status, slot < 0 ? 1 : 2);
-    return;
-  }
+  const int a = t < ntiles ? t / tpe : -1, rt = t - a * tpe;
+  TileExpert te;
+  if (!tile_expert<SEL>(a, rt == 0, outputs, ep, work, q, te)) return;
   const int r16 = lane & 15, kg = lane >> 4;
-  const bool bv = r16 < 3 && wk.n > 0;
-  const int xe = bv ? wk.xe[0] : 0;
+  const bool bv = r16 < 3 && te.any;
+  const int xe = te.xe;
   const int8_t* xr = xl + (size_t)(bv ? r16 : 0) * ld + kg * 16;
   const auto load_x = [&](int, int ks) { return bv ? *(const v4i*)(xr + ks * 64) : zero16(); };
   float accg[1][4], accu[1][4];
   const bool bva[1] = {bv};
-  gateup_tile_stream_i4<1, kTileI4Unroll, true>(C, R, rt, (const uint8_t*)ep.pool + (size_t)slot * ep.stride,
+  gateup_tile_stream_i4<1, kTileI4Unroll, true>(C, R, rt, (const uint8_t*)ep.pool + (size_t)te.slot * ep.stride,
                                                 bva, load_x, accg, accu);
   // 2^-E of the token's fixed point, and 1/16 for the nibble operand (16*q)
   const bool lead = bv && r16 == 0;
@@ -254,7 +348,7 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_i4_kern
     const float h = gv / (1.f + expf(-gv)) * uv;
     hv[i] = lead ? h : 0.f;
   }
-  write_h_tile_1tok(R, rt, wk.off, lead, hv, hdig, hexp);
+  write_h_tile_1tok(R, rt, te.off, lead, hv, hdig, hexp);
 }
 
 // ---------------------------------------------------------------------------
@@ -530,17 +624,18 @@ static void launch_decode_gateup(const Layout& L, const WsPtr& w, const ExpertPo
 
 // One token: the 16-row tiles of all active experts split evenly over the
 // CUs (W waves per workgroup, about one workgroup per CU), and the down
-// kernel reads per-tile exponents.
+// kernel reads per-tile exponents.  q: the selection, if gate/up makes it.
 template <bool I4>
 static void launch_decode_ffn_1tok(const Layout& L, const WsPtr& w, const ExpertPool& ep,
-                                   float* out, hipStream_t st) {
+                                   const OneTokenSel* q, float* out, hipStream_t st) {
   const int ntiles = decode_max_active(L) * (L.R / 16);
   const int cus = device_cu_count();
   const int W = std::min(kTileMaxWaves, (ntiles + cus - 1) / cus);
   const int nwg = (ntiles + W - 1) / W;
-  launch_timed("decode_gateup", I4 ? decode_gateup_tile_i4_kernel : decode_gateup_tile_kernel,
-               dim3(nwg), dim3(64 * W), 0, st, L.C, L.R, W, ntiles, ep, w.dwork, w.xdig, w.hdig,
-               w.hexp);
+  const auto kern = I4 ? (q ? decode_gateup_tile_i4_kernel<true> : decode_gateup_tile_i4_kernel<false>)
+                       : (q ? decode_gateup_tile_kernel<true> : decode_gateup_tile_kernel<false>);
+  launch_timed("decode_gateup", kern, dim3(nwg), dim3(64 * W), 0, st, L.C, L.R, W, ntiles, ep,
+               w.dwork, q ? *q : OneTokenSel{}, w.xdig, w.hdig, w.hexp);
   launch_decode_down_ng<1, I4, 3, true>(L, w, ep, out, st);
 }
 
@@ -548,7 +643,7 @@ template <bool I4>
 static void launch_decode_ffn(const Layout& L, const WsPtr& w, const ExpertPool& ep, float* out,
                               hipStream_t st) {
   if (L.T == 1 && (!I4 || L.C <= kXlMaxC)) {
-    launch_decode_ffn_1tok<I4>(L, w, ep, out, st);
+    launch_decode_ffn_1tok<I4>(L, w, ep, nullptr, out, st);
     return;
   }
   // token groups of an expert (each holds at most T tokens): 5 tokens per x
@@ -579,6 +674,25 @@ hipError_t launch_decode(const mira_shape& s, const Layout& L, const WsPtr& w, c
     launch_decode_ffn<true>(L, w, ep, out, st);
   else
     launch_decode_ffn<false>(L, w, ep, out, st);
+  return hipGetLastError();
+}
+
+bool one_token_fused(const mira_shape& s, const Layout& L) {
+  return L.T == 1 && L.E <= 64 && L.k + L.S <= 64 && (!(s.flags & MIRA_FLAG_INT4) || L.C <= kXlMaxC);
+}
+
+hipError_t launch_one_token(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,
+                            const void* wr, const float* bias, float* logits_out,
+                            const ExpertPool& ep, int32_t* counts_out, int32_t* idx_out,
+                            float* wts_out, int32_t* offsets_out, int32_t* order_out, float* out,
+                            hipStream_t st) {
+  launch_decode_logits(s, L, w, x, wr, bias, logits_out, st);
+  const OneTokenSel q{w.logits, decode_xe(w), L.E, L.k, L.S, (s.flags & MIRA_FLAG_SOFTMAX_ALL) ? 1 : 0,
+                      perm_out(w, counts_out, idx_out, wts_out, offsets_out, order_out)};
+  if (s.flags & MIRA_FLAG_INT4)
+    launch_decode_ffn_1tok<true>(L, w, ep, &q, out, st);
+  else
+    launch_decode_ffn_1tok<false>(L, w, ep, &q, out, st);
   return hipGetLastError();
 }
 

@@ -496,6 +496,13 @@ int mira_moe_forward(const mira_shape* s, const mira_moe_args* a, hipStream_t st
   int rc = check_args(s, a, &L);
   if (rc) return rc;
   if (a->n_tokens == 0) return ok();
+  if (use_decode(*s, L.T) && mira::one_token_fused(*s, L)) {
+    HIP_TRY(mira::launch_one_token(*s, L, mira::ws_ptrs(L, a->workspace), a->x, a->w_router,
+                                   a->router_bias, a->logits, pool_of(a), a->expert_counts,
+                                   a->topk_idx, a->topk_weight, a->expert_offsets, a->pair_order,
+                                   a->out, stream));
+    return ok();
+  }
   rc = run_route(s, a, L, stream);
   if (rc) return rc;
   rc = run_experts(s, a, L, stream);

@@ -193,6 +193,11 @@ inline WsPtr ws_ptrs(const Layout& L, void* base) {
   return w;
 }
 
+// The tokens' fixed-point exponents of a decode call whose logits are a launch
+// of their own (the region holds chunk counts in prefill calls).
+static_assert(kPermChunkMax >= MIRA_DECODE_MAX_TOKENS, "exponents fit");
+inline int32_t* decode_xe(const WsPtr& w) { return w.pcnt; }
+
 inline int decode_max_active(const Layout& L) { return decode_max_active_of(L.G, L.T, L.k, L.S); }
 
 // Everything the expert kernels need to find a packed expert.
@@ -234,6 +239,17 @@ hipError_t launch_decode_prep(const mira_shape& s, const Layout& L, const WsPtr&
                               const ExpertPool& ep, int32_t* counts_out, int32_t* idx_out,
                               float* wts_out, int32_t* offsets_out, int32_t* order_out,
                               hipStream_t st);
+// Router logits (w.logits), digits and exponents (decode_xe) of a decode call.
+void launch_decode_logits(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,
+                          const void* wr, const float* bias, float* logits_out, hipStream_t st);
+// Whether a one-token layer call may run as logits, gate/up (which selects the
+// experts itself) and down, and that call.
+bool one_token_fused(const mira_shape& s, const Layout& L);
+hipError_t launch_one_token(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,
+                            const void* wr, const float* bias, float* logits_out,
+                            const ExpertPool& ep, int32_t* counts_out, int32_t* idx_out,
+                            float* wts_out, int32_t* offsets_out, int32_t* order_out, float* out,
+                            hipStream_t st);
 hipError_t launch_decode(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,
                          const ExpertPool& ep, float* out, hipStream_t st);
 hipError_t launch_prefill(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,

@@ -9,8 +9,8 @@
 //    and topk_kernel; then the permutation (one workgroup, or count and
 //    scatter kernels over chunks of pairs);
 //  - decode (T <= MIRA_DECODE_MAX_TOKENS): one workgroup runs router, top-k,
-//    permutation and the fixed-point digits of x back to back, so the
-//    expert kernels start after a single small launch.
+//    permutation back to back beside one per token for the digits of x; large
+//    routers in two launches.
 #include "route_dev.h"
 
 namespace mira {
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kBigThreads) void route_kernel(
   if constexpr (sizeof(ActT) == 2) {
     logits_ksplit_bf16(x + (size_t)t0 * C, wr, bias_s, nt, E, C, part, lg, nullptr, stage);
   } else {
-    logits_tile_f32(x, wr, bias, T, E, C, t0, kBigWaves, lg);
+    logits_f32(x + (size_t)t0 * C, wr, bias, nt, C, 0, E, kBigWaves, lg);
     __syncthreads();
   }
   if (wave < nt) {
@@ -392,13 +392,19 @@ __global__ __launch_bounds__(kBigThreads) void permute_kernel(const int32_t* __r
 
 
 // ---------------------------------------------------------------------------
-// Decode preparation (T <= 16 tokens, one workgroup): router logits (with
-// max |x| per token on the way), top-k and weights; then wave 0 groups the
-// pairs (with wave 1 writing the optional outputs when there are at most 64
-// pairs) while the other waves write the fixed-point digits of x used by the
-// integer expert kernels (|x * 2^E_t| < 2^22 per token, three signed
-// base-256 digits; layout xdig[(t*3 + d)*C + c]; the exponent E_t goes into
-// the expert descriptors).
+// Decode preparation (T <= 16 tokens).  The routing: router logits, top-k and
+// weights, the expert kernels' descriptors (wave 0) and the optional outputs
+// (wave 1 when there are at most 64 pairs).  Beside it, one workgroup per
+// token writes the fixed-point digits of x used by the integer expert kernels
+// (|x * 2^E_t| < 2^22 per token, three signed base-256 digits; layout
+// xdig[(t*3 + d)*C + c]; the exponent E_t goes into the expert descriptors).
+//
+// A small router is one workgroup of the same launch (decode_prep_kernel).
+// With several expert tiles and kSplitRouterBytes of rows, one CU's loads would
+// set the time, so a first launch computes each tile's logits in a workgroup
+// of its own (decode_logits_kernel) and a second one selects
+// (decode_select_kernel).  A whole one-token layer call needs no selection
+// launch at all: its gate/up kernel selects (one_token_fused).
 // ---------------------------------------------------------------------------
 // Fixed-point digits (exponent Ex) of elements 4*i .. 4*i+3 of one token's x
 // row xr, into that token's three digit rows xd[d*C + c].
@@ -422,50 +428,115 @@ __device__ __forceinline__ void write_x_digits4(const ActT* __restrict__ xr, int
   *(uint32_t*)(xd + 2 * (size_t)C + c) = w2;
 }
 
+// The digits of one token's row by one workgroup; returns its exponent.
+template <typename ActT>
+__device__ __forceinline__ int token_digits(const ActT* __restrict__ xr, int C,
+                                            int8_t* __restrict__ xd) {
+  __shared__ float wmax[kBigWaves];
+  const int tid = threadIdx.x;
+  float m = 0.f;
+  for (int i = tid; i < C / 4; i += kBigThreads) {
+    float v[4];
+    load4_act(xr + i * 4, v);
+    m = fmaxf(m, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+  }
+  m = wave_max(m);
+  if ((tid & 63) == 0) wmax[tid >> 6] = m;
+  __syncthreads();
+  m = wmax[0];
+  for (int w = 1; w < kBigWaves; ++w) m = fmaxf(m, wmax[w]);
+  const int Ex = kFixBits - exp_bound(m);
+  for (int i = tid; i < C / 4; i += kBigThreads) write_x_digits4(xr, i, Ex, xd, C);
+  return Ex;
+}
+
+// A call whose selection is one wave's registers and has no barrier.
+__host__ __device__ constexpr bool one_token_small(int T, int E, int k, int S) {
+  return T == 1 && E <= 64 && k + S <= 64;
+}
+
+// LDS of the selection step, after the logits.
+struct SelectLds {
+  int32_t idx[kRouteTok * MIRA_MAX_TOPK];
+  float w[kRouteTok * MIRA_MAX_TOPK];
+  int xe[kRouteTok];
+  int cnt[MIRA_MAX_EXPERTS], run[MIRA_MAX_EXPERTS];
+  int ptok[kDecodeMaxPairs];
+  float pw[kDecodeMaxPairs];
+  int slot[MIRA_MAX_EXPERTS];
+  int sel_e[kRouteTok][MIRA_MAX_TOPK];
+  float sel_v[kRouteTok][MIRA_MAX_TOPK];
+};
+
+// Top-k, descriptors and optional outputs of T tokens from their logits (row
+// stride ld; LDS or workspace) and exponents (sh.xe) by one workgroup; the
+// logits, sh.xe and sh.slot are visible to it.
+__device__ __forceinline__ void decode_select(const float* lg, int ld, int T, int E, int k, int S,
+                                              int softmax_all, const ExpertPool& ep,
+                                              const PermOut& o, DecodeWork* __restrict__ work,
+                                              int max_active, SelectLds& sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (one_token_small(T, E, k, S)) {
+    // nothing waits after the logits.  Wave 0 selects and writes
+    // the descriptors from registers; wave 1 makes the same selection (same
+    // keys, same order) for the optional outputs.
+    if (wave == 0) {
+      decode_work_one_token(lg, E, k, S, softmax_all, sh.xe[0], sh.slot, ep, work, max_active);
+    } else if (wave == 1) {
+      topk_rank(lg, E, k, softmax_all, sh.idx, sh.w, sh.sel_e[0], sh.sel_v[0]);
+      decode_outputs_small(sh.idx, sh.w, 1, k, E, S, o, sh.cnt);
+    }
+    return;
+  }
+  if (wave < T)
+    topk_rank(lg + (size_t)wave * ld, E, k, softmax_all, sh.idx + wave * k, sh.w + wave * k,
+              sh.sel_e[wave], sh.sel_v[wave]);
+  lds_barrier();  // the routing is in LDS; no global data is read after this
+
+  // up to 64 pairs: wave 0 writes the expert kernels' descriptors and wave 1
+  // the optional outputs side by side; otherwise wave 0 does both
+  const bool small = T * k <= kDecodeSmallPairs;
+  if (wave == 0) {
+    if (small)
+      decode_work_small(sh.idx, sh.w, sh.xe, sh.slot, T, k, E, S, ep, work, max_active);
+    else
+      permute_decode_wave(sh.idx, sh.w, sh.xe, sh.slot, T, k, E, S, ep, o, work, max_active, sh.cnt,
+                          sh.run, sh.ptok, sh.pw);
+  } else if (small && wave == 1) {
+    decode_outputs_small(sh.idx, sh.w, T, k, E, S, o, sh.cnt);
+  }
+}
+
 template <typename ActT>
 __global__ __launch_bounds__(kBigThreads) void decode_prep_kernel(
     const ActT* __restrict__ x, const ActT* __restrict__ wr, const float* __restrict__ bias,
     int T, int E, int C, int k, int S, int softmax_all, float* __restrict__ logits_out,
     ExpertPool ep, PermOut o, DecodeWork* __restrict__ work, int max_active,
     int8_t* __restrict__ xdig) {
+  if (blockIdx.x > 0) {  // blocks 1 .. T: the digits of token blockIdx.x - 1
+    const int t = blockIdx.x - 1;
+    token_digits(x + (size_t)t * C, C, xdig + (size_t)t * kDigits * C);
+    return;
+  }
   __shared__ float lg[kRouteTok][MIRA_MAX_EXPERTS];
   __shared__ float part[kBigWaves][16][17];
-  __shared__ int32_t idx_s[kRouteTok * MIRA_MAX_TOPK];
-  __shared__ float w_s[kRouteTok * MIRA_MAX_TOPK];
   __shared__ float xmax[kRouteTok];
-  __shared__ int xe_s[kRouteTok];
-  __shared__ int cnt_s[MIRA_MAX_EXPERTS], run_s[MIRA_MAX_EXPERTS];
-  __shared__ int ptok_s[kDecodeMaxPairs];
-  __shared__ float pw_s[kDecodeMaxPairs];
   __shared__ float bias_s[MIRA_MAX_EXPERTS];
-  __shared__ int slot_s[MIRA_MAX_EXPERTS];
-  __shared__ int sel_e[kRouteTok][MIRA_MAX_TOPK];
-  __shared__ float sel_v[kRouteTok][MIRA_MAX_TOPK];
+  __shared__ SelectLds sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // load the router bias and the slot table into registers now and store
   // them to LDS just before the logits barrier, so the loads overlap
-  float bias_r[MIRA_MAX_EXPERTS / kBigThreads + 1];
-  int slot_r[MIRA_MAX_EXPERTS / kBigThreads + 1];
-#pragma unroll
-  for (int i = 0; i <= MIRA_MAX_EXPERTS / kBigThreads; ++i) {
-    const int e = tid + i * kBigThreads;
-    bias_r[i] = (bias && e < E) ? bias[e] : 0.f;
-    slot_r[i] = e < E + S ? ep.slot_table[e] : 0;
-  }
+  const float bias_r = (bias && tid < E) ? bias[tid] : 0.f;
+  const int slot_r = tid < E + S ? ep.slot_table[tid] : 0;
   auto stage = [&]() {
-#pragma unroll
-    for (int i = 0; i <= MIRA_MAX_EXPERTS / kBigThreads; ++i) {
-      const int e = tid + i * kBigThreads;
-      if (e < E) bias_s[e] = bias_r[i];
-      if (e < E + S) slot_s[e] = slot_r[i];
-    }
+    if (tid < E) bias_s[tid] = bias_r;
+    if (tid < E + S) sh.slot[tid] = slot_r;
   };
-
   if constexpr (sizeof(ActT) == 2) {
     logits_ksplit_bf16(x, wr, bias_s, T, E, C, part, lg, xmax, stage);
   } else {
     stage();
-    logits_tile_f32(x, wr, bias, T, E, C, 0, kBigWaves, lg);
+    logits_f32(x, wr, bias, T, C, 0, E, kBigWaves, lg);
     if (wave < T) {  // one wave per token: max |x|
       float m = 0.f;
       for (int c = lane * 4; c < C; c += 256) {
@@ -478,57 +549,74 @@ __global__ __launch_bounds__(kBigThreads) void decode_prep_kernel(
     }
     __syncthreads();
   }
-  if (T == 1 && E <= 64 && k + S <= 64) {
-    // one token: nothing waits after the logits.  Wave 0 selects and writes
-    // the descriptors from registers; wave 1 makes the same selection (same
-    // keys, same order) for the optional outputs; the other waves write the
-    // digits of x.
-    const int xe = kFixBits - exp_bound(xmax[0]);
-    if (wave == 0) {
-      decode_work_one_token(lg[0], E, k, S, softmax_all, xe, slot_s, ep, work, max_active);
-    } else if (wave == 1) {
-      if (logits_out)
-        for (int e = lane; e < E; e += 64) logits_out[e] = lg[0][e];
-      topk_rank(lg[0], E, k, softmax_all, idx_s, w_s, sel_e[0], sel_v[0]);
-      decode_outputs_small(idx_s, w_s, 1, k, E, S, o, cnt_s);
-    } else {
-      for (int i = tid - 128; i < C / 4; i += kBigThreads - 128) write_x_digits4(x, i, xe, xdig, C);
+  if (logits_out && wave < T)
+    for (int e = lane; e < E; e += 64) logits_out[(size_t)wave * E + e] = lg[wave][e];
+  if (tid < T) sh.xe[tid] = kFixBits - exp_bound(xmax[tid]);
+  if (gridDim.x == 1) {
+    // one_token_small: wave 0 reads the exponent that it wrote,
+    // and the waves that select nothing write the digits
+    __builtin_amdgcn_wave_barrier();
+    if (wave >= 2) {
+      const int Ex = kFixBits - exp_bound(xmax[0]);
+      for (int i = tid - 128; i < C / 4; i += kBigThreads - 128) write_x_digits4(x, i, Ex, xdig, C);
+      return;
     }
-    return;
+  } else {
+    lds_barrier();
   }
-  if (wave < T) {
-    const int t = wave;
-    if (logits_out)
-      for (int e = lane; e < E; e += 64) logits_out[(size_t)t * E + e] = lg[t][e];
-    topk_rank(lg[t], E, k, softmax_all, idx_s + t * k, w_s + t * k, sel_e[t], sel_v[t]);
-  }
-  if (tid < T) xe_s[tid] = kFixBits - exp_bound(xmax[tid]);
-  lds_barrier();  // the routing and exponents are in LDS; no global data is read after this
+  decode_select(&lg[0][0], MIRA_MAX_EXPERTS, T, E, k, S, softmax_all, ep, o, work, max_active, sh);
+}
 
-  // up to 64 pairs: wave 0 writes the expert kernels' descriptors and wave 1
-  // the optional outputs side by side; otherwise wave 0 does both
-  const bool small = T * k <= kDecodeSmallPairs;
-  if (wave == 0) {
-    if (small)
-      decode_work_small(idx_s, w_s, xe_s, slot_s, T, k, E, S, ep, work, max_active);
-    else
-      permute_decode_wave(idx_s, w_s, xe_s, slot_s, T, k, E, S, ep, o, work, max_active, cnt_s,
-                          run_s, ptok_s, pw_s);
+// Blocks 0 .. n_et-1: the logits of one tile of 16 experts, summed exactly as
+// in the one-workgroup form.  Blocks n_et .. n_et+T-1: the digits and exponent
+// of one token.
+template <typename ActT>
+__global__ __launch_bounds__(kBigThreads) void decode_logits_kernel(
+    const ActT* __restrict__ x, const ActT* __restrict__ wr, const float* __restrict__ bias,
+    int T, int E, int C, float* __restrict__ logits_ws, float* __restrict__ logits_out,
+    int32_t* __restrict__ xe_ws, int8_t* __restrict__ xdig) {
+  const int n_et = (E + 15) / 16, et = blockIdx.x, tid = threadIdx.x;
+  if (et >= n_et) {
+    const int t = et - n_et;
+    const int Ex = token_digits(x + (size_t)t * C, C, xdig + (size_t)t * kDigits * C);
+    if (tid == 0) xe_ws[t] = Ex;
     return;
   }
-  if (small && wave == 1) {
-    decode_outputs_small(idx_s, w_s, T, k, E, S, o, cnt_s);
-    return;
+  __shared__ float lg[kRouteTok][MIRA_MAX_EXPERTS];
+  __shared__ float part[kBigWaves][16][17];
+  __shared__ float bias_s[MIRA_MAX_EXPERTS];
+  const int e_lo = et * 16, ne = min(16, E - e_lo);
+  if constexpr (sizeof(ActT) == 2) {
+    const float b_r = (bias && tid < ne) ? bias[e_lo + tid] : 0.f;
+    auto stage = [&]() {
+      if (tid < ne) bias_s[e_lo + tid] = b_r;
+    };
+    logits_ksplit_bf16(x, wr, bias_s, T, E, C, part, lg, nullptr, stage, et, et + 1);
+  } else {
+    logits_f32(x, wr, bias, T, C, e_lo, e_lo + ne, kBigWaves, lg);
+    __syncthreads();
   }
-  // the other waves: fixed-point digits of x, four elements per thread and step
-  const int w0d = small ? 2 : 1;
-  const int q4 = C / 4, n4 = T * q4;
-  for (int i = tid - 64 * w0d; i < n4; i += kBigThreads - 64 * w0d) {
-    const int t = i / q4;
-    write_x_digits4(x + (size_t)t * C, i - t * q4, xe_s[t], xdig + (size_t)t * kDigits * C, C);
+  if (tid < T * 16) {
+    const int tt = tid >> 4, ee = tid & 15;
+    if (ee < ne) {
+      const size_t i = (size_t)tt * E + e_lo + ee;
+      logits_ws[i] = lg[tt][e_lo + ee];
+      if (logits_out) logits_out[i] = lg[tt][e_lo + ee];
+    }
   }
 }
 
+__global__ __launch_bounds__(kBigThreads) void decode_select_kernel(
+    const float* __restrict__ logits_ws, const int32_t* __restrict__ xe_ws, int T, int E, int k,
+    int S, int softmax_all, ExpertPool ep, PermOut o, DecodeWork* __restrict__ work,
+    int max_active) {
+  __shared__ SelectLds sh;
+  const int tid = threadIdx.x;
+  if (tid < E + S) sh.slot[tid] = ep.slot_table[tid];
+  if (tid < T) sh.xe[tid] = xe_ws[tid];
+  __syncthreads();
+  decode_select(logits_ws, E, T, E, k, S, softmax_all, ep, o, work, max_active, sh);
+}
 
 hipError_t launch_route(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,
                         const void* wr, const float* bias, float* logits_out, hipStream_t st) {
@@ -539,7 +627,10 @@ hipError_t launch_route(const mira_shape& s, const Layout& L, const WsPtr& w, co
   // sums do not depend on which other tokens share its MFMA operand.  With
   // several tiles, more workgroups would re-read every tile's rows.
   const int n_et = (L.E + 15) / 16;
-  const int tpw = (s.act_dtype == MIRA_BF16 && n_et == 1) ? kRouteTokBf16 : kRouteTok;
+  // fp32: four tokens (one pass of a wave) per workgroup until that fills the
+  // CUs.
+  const bool few = s.act_dtype == MIRA_BF16 ? n_et == 1 : T <= kRouteTokFew * device_cu_count();
+  const int tpw = few ? kRouteTokFew : kRouteTok;
   dim3 grid((T + tpw - 1) / tpw), block(kBigThreads);
   const int sa = (s.flags & MIRA_FLAG_SOFTMAX_ALL) ? 1 : 0;
   prof_begin("route", st);
@@ -580,6 +671,26 @@ hipError_t launch_permute(const Layout& L, const WsPtr& w,
   return hipGetLastError();
 }
 
+static void launch_logits(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,
+                          const void* wr, const float* bias, float* logits_out, hipStream_t st) {
+  const dim3 grid((L.E + 15) / 16 + L.T);
+  if (s.act_dtype == MIRA_BF16)
+    hipLaunchKernelGGL(decode_logits_kernel<uint16_t>, grid, dim3(kBigThreads), 0, st,
+                       (const uint16_t*)x, (const uint16_t*)wr, bias, L.T, L.E, L.C, w.logits,
+                       logits_out, decode_xe(w), w.xdig);
+  else
+    hipLaunchKernelGGL(decode_logits_kernel<float>, grid, dim3(kBigThreads), 0, st, (const float*)x,
+                       (const float*)wr, bias, L.T, L.E, L.C, w.logits, logits_out, decode_xe(w),
+                       w.xdig);
+}
+
+// Router bytes from which a decode call's logits are a launch of their own:
+// us per layer call in one launch / in two, one launch costing about 2 us more
+// than none: 70 KB (17 experts of C = 1024) 17.4 / 20.9 with one token, 96 KB
+// 35.0 / 34.8 with 4 tokens and 62.2 / 60.8 with 16, 160 KB 88.9 / 85.3 with
+// 16, 256 KB 55.3 / 49.8 with 4 and 102 / 93 with 16.
+constexpr size_t kSplitRouterBytes = 96 << 10;
+
 hipError_t launch_decode_prep(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,
                               const void* wr, const float* bias, float* logits_out,
                               const ExpertPool& ep, int32_t* counts_out, int32_t* idx_out,
@@ -589,17 +700,32 @@ hipError_t launch_decode_prep(const mira_shape& s, const Layout& L, const WsPtr&
   const int sa = (s.flags & MIRA_FLAG_SOFTMAX_ALL) ? 1 : 0;
   const PermOut o = perm_out(w, counts_out, idx_out, wts_out, offsets_out, order_out);
   const int max_active = decode_max_active(L);
+  const bool bf16 = s.act_dtype == MIRA_BF16;
+  const int blocks = one_token_small(L.T, L.E, L.k, L.S) ? 1 : 1 + L.T;
   prof_begin("decode_prep", st);
-  if (s.act_dtype == MIRA_BF16)
-    hipLaunchKernelGGL(decode_prep_kernel<uint16_t>, dim3(1), dim3(kBigThreads), 0, st,
+  if (L.E > 16 && (size_t)L.E * L.C * (bf16 ? 2 : 4) >= kSplitRouterBytes) {
+    launch_logits(s, L, w, x, wr, bias, logits_out, st);
+    hipLaunchKernelGGL(decode_select_kernel, dim3(1), dim3(kBigThreads), 0, st,
+                       (const float*)w.logits, (const int32_t*)decode_xe(w), L.T, L.E, L.k, L.S, sa,
+                       ep, o, w.dwork, max_active);
+  } else if (bf16) {
+    hipLaunchKernelGGL(decode_prep_kernel<uint16_t>, dim3(blocks), dim3(kBigThreads), 0, st,
                        (const uint16_t*)x, (const uint16_t*)wr, bias, L.T, L.E, L.C, L.k, L.S, sa,
                        logits_out, ep, o, w.dwork, max_active, w.xdig);
-  else
-    hipLaunchKernelGGL(decode_prep_kernel<float>, dim3(1), dim3(kBigThreads), 0, st,
+  } else {
+    hipLaunchKernelGGL(decode_prep_kernel<float>, dim3(blocks), dim3(kBigThreads), 0, st,
                        (const float*)x, (const float*)wr, bias, L.T, L.E, L.C, L.k, L.S, sa,
                        logits_out, ep, o, w.dwork, max_active, w.xdig);
+  }
   prof_end("decode_prep", st);
   return hipGetLastError();
+}
+
+void launch_decode_logits(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,
+                          const void* wr, const float* bias, float* logits_out, hipStream_t st) {
+  prof_begin("decode_logits", st);
+  launch_logits(s, L, w, x, wr, bias, logits_out, st);
+  prof_end("decode_logits", st);
 }
 
 // A whole slot-table row, passed by value (at most MIRA_MAX_EXPERTS entries).

@@ -10,32 +10,74 @@
 namespace mira {
 
 constexpr int kRouteTok = 16;  // tokens per route workgroup (at most)
-constexpr int kRouteTokBf16 = 4;  // tokens per prefill route workgroup, bf16, one expert tile
+constexpr int kRouteTokFew = 4;  // tokens per prefill route workgroup where more workgroups help
 constexpr int kBigThreads = 1024;  // permutation and decode-prep workgroups
 static_assert(kPermChunk == kBigThreads, "the chunked permutation runs one thread per pair");
 constexpr int kBigWaves = kBigThreads / 64;
 
 // ---------------------------------------------------------------------------
 // Router logits for 16 tokens: lg[t][e] = sum_c x[t][c] * Wg[e][c] + b[e].
-// fp32: VALU dot products, one wave per (token, expert), fp32 accumulate.
+// fp32 (logits_f32): VALU dot products, fp32 accumulate.
 // bf16 (below): MFMA, A = Wg rows (experts), B = x rows (tokens), fp32
 // accumulate, the k range split over the waves.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void logits_tile_f32(const float* __restrict__ x,
-                                                const float* __restrict__ wr,
-                                                const float* __restrict__ bias, int T, int E,
-                                                int C, int t0, int nwaves,
-                                                float (*lg)[MIRA_MAX_EXPERTS]) {
+// fp32 logits of nt <= 16 tokens from row x on, experts e_begin .. e_end-1, by
+// a workgroup of nwaves waves: a wave takes 4 tokens x 4 experts at a time and
+// reads their rows with 16-byte loads, so that a router row serves four tokens
+// and a wave has up to 20 loads in flight (one token and expert at a time, with
+// 4-byte loads, this was bound by load latency: 301 tokens x 16 experts x 1024
+// took 106 us).  A logit's sum does not depend on the tile it is computed in:
+// lane l adds columns 256 i + 4 l + j in the order of (i, j), then the lanes add.
+__device__ __forceinline__ void logits_f32(const float* __restrict__ x,
+                                           const float* __restrict__ wr,
+                                           const float* __restrict__ bias, int nt, int C,
+                                           int e_begin, int e_end, int nwaves,
+                                           float (*lg)[MIRA_MAX_EXPERTS]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ntok = min(kRouteTok, T - t0);
-  for (int pr = wave; pr < ntok * E; pr += nwaves) {
-    const int tt = pr / E, e = pr - tt * E;
-    const float* xr = x + (size_t)(t0 + tt) * C;
-    const float* wrow = wr + (size_t)e * C;
-    float s = 0.f;
-    for (int c = lane; c < C; c += 64) s = fmaf(xr[c], wrow[c], s);
-    s = wave_sum(s);
-    if (lane == 0) lg[tt][e] = s + (bias ? bias[e] : 0.f);
+  const int nq = (nt + 3) / 4, ne = (e_end - e_begin + 3) / 4;
+  constexpr int B = 2;  // 256-column chunks in flight
+  for (int it = wave; it < nq * ne; it += nwaves) {
+    const int t0 = (it % nq) * 4, e0 = e_begin + (it / nq) * 4;
+    const float *xr[4], *wrow[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      xr[j] = x + (size_t)min(t0 + j, nt - 1) * C + lane * 4;
+      wrow[j] = wr + (size_t)min(e0 + j, e_end - 1) * C + lane * 4;
+    }
+    float acc[4][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t][e] = 0.f;
+    for (int c0 = 0; c0 < C; c0 += 256 * B) {
+      v4f xv[B][4], wv[B][4];
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const int c = c0 + 256 * b;
+        const bool in = c + lane * 4 < C;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          xv[b][j] = in ? *(const v4f*)(xr[j] + c) : v4f{0.f, 0.f, 0.f, 0.f};
+          wv[b][j] = in ? *(const v4f*)(wrow[j] + c) : v4f{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[t][e] = fmaf(xv[b][t][j], wv[b][e][j], acc[t][e]);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float s = wave_sum(acc[t][e]);
+        if (lane == 0 && t0 + t < nt && e0 + e < e_end)
+          lg[t0 + t][e0 + e] = s + (bias ? bias[e0 + e] : 0.f);
+      }
   }
 }
 
@@ -144,6 +186,70 @@ __device__ void logits_ksplit_bf16(const uint16_t* __restrict__ x, const uint16_
   }
 }
 
+// Largest value over the wave (uniform result), by DPP row shifts and
+// broadcasts: lanes without a source take 0.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  const auto up = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+  v = up(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));  // row_shr:1
+  v = up(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));  // row_shr:2
+  v = up(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));  // row_shr:4
+  v = up(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));  // row_shr:8
+  v = up(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  v = up(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The selection of topk_rank with E <= 64 experts, one per lane: lane e
+// learns whether it is selected, its position and its combine weight.  From
+// E = 2k on, the largest key k times (ties to the lower lane): a chain of k
+// maxima, about eight dependent instructions each, where counting every
+// expert's rank takes E steps (64 experts top-6: the one-token gate/up kernel,
+// which selects first, 15.3 -> 13.3 us; with E = k = 16 counting is 1 us ahead).
+__device__ __forceinline__ void topk_lane64(const float* lgrow, int E, int k, int softmax_all,
+                                            bool& sel, int& rank, float& w) {
+  const int lane = threadIdx.x & 63;
+  const bool in = lane < E;
+  const float v = in ? lgrow[lane] : 0.f;
+  const uint32_t key = f32_order_key(v);
+  const auto lane_f = [](float x, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+  };
+  float ex = 0.f, denom = 0.f;
+  const auto first = [&](int l) {  // exponentials against the largest logit
+    ex = in ? expf(v - lane_f(v, l)) : 0.f;
+    if (softmax_all) denom = wave_sum(ex);
+  };
+  rank = 0;
+  if (E >= 2 * k) {
+    sel = false;
+#pragma unroll 1
+    for (int j = 0; j < k; ++j) {
+      const bool open = in && !sel;
+      const uint32_t top = wave_max_u32(open ? key : 0u);
+      const int l = __builtin_ctzll(__ballot(open && key == top));
+      if (j == 0) first(l);
+      if (!softmax_all) denom += lane_f(ex, l);
+      if (lane == l) {
+        sel = true;
+        rank = j;
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int l2 = 0; l2 < E; ++l2) {
+      const uint32_t k2 = (uint32_t)__builtin_amdgcn_readlane((int)key, l2);
+      rank += (k2 > key) || (k2 == key && l2 < lane);
+    }
+    sel = in && rank < k;
+    first(__builtin_ctzll(__ballot(sel && rank == 0)));
+    if (!softmax_all) {
+#pragma unroll 1
+      for (int j = 0; j < k; ++j) denom += lane_f(ex, __builtin_ctzll(__ballot(sel && rank == j)));
+    }
+  }
+  w = ex / denom;
+}
+
 // Top-k of one token by rank counting (one wave): expert e is selected at
 // position rank(e) = number of experts with a larger (value, then lower
 // index) key, if that is < k.  Each lane holds the logits of its experts
@@ -151,37 +257,6 @@ __device__ void logits_ksplit_bf16(const uint16_t* __restrict__ x, const uint16_
 // v_readlane, so the count needs no memory round trips.  The combine weights
 // are a softmax in fp32, summed in selection order.  sel_e/sel_v: this wave's
 // LDS scratch.
-// The selection of topk_rank with E <= 64 experts, one per lane: lane e
-// learns whether it is selected, its position and its combine weight.
-__device__ __forceinline__ void topk_lane64(const float* lgrow, int E, int k, int softmax_all,
-                                            bool& sel, int& rank, float& w) {
-  const int lane = threadIdx.x & 63;
-  const bool in = lane < E;
-  const float v = in ? lgrow[lane] : 0.f;
-  const uint32_t key = f32_order_key(v);
-  rank = 0;
-#pragma unroll 1
-  for (int l2 = 0; l2 < E; ++l2) {
-    const uint32_t k2 = (uint32_t)__builtin_amdgcn_readlane((int)key, l2);
-    rank += (k2 > key) || (k2 == key && l2 < lane);
-  }
-  sel = in && rank < k;
-  const int l0 = __builtin_ctzll(__ballot(sel && rank == 0));
-  const float vmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l0));
-  const float ex = in ? expf(v - vmax) : 0.f;
-  float denom = 0.f;
-  if (softmax_all) {
-    denom = wave_sum(ex);
-  } else {
-#pragma unroll 1
-    for (int j = 0; j < k; ++j) {
-      const int lj = __builtin_ctzll(__ballot(sel && rank == j));
-      denom += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ex), lj));
-    }
-  }
-  w = ex / denom;
-}
-
 __device__ __forceinline__ void topk_rank(const float* lgrow, int E, int k, int softmax_all,
                                           int32_t* idx_a, float* w_a, int* sel_e, float* sel_v) {
   constexpr int kPer = MIRA_MAX_EXPERTS / 64;  // experts per lane

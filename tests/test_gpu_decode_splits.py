@@ -8,7 +8,12 @@ an expert of at most one token group runs the one-group body.
 
 Gate/up: an expert's own token count (1 to 5, to 10, above) chooses the body
 in a call of several groups (INT8 up to 15 tokens, INT4 always); INT4 keeps the
-digits of one-group experts in LDS up to hidden 4096."""
+digits of one-group experts in LDS up to hidden 4096.
+
+Routing: large routers (more than 16 experts and 96 KB of rows) compute their
+logits in a launch of their own; a whole one-token call with at most 64 experts
+selects inside the gate/up kernel."""
+import numpy as np
 import pytest
 
 from gpu_layer import Layer, decode_rel_floor, run_and_check
@@ -65,3 +70,42 @@ GATEUP = [
 def test_gateup_groups(mira, cfg, fmt):
     _, errs, _, _ = run_and_check(Layer(cfg, fmt=fmt))
     assert errs[0] < decode_rel_floor(cfg.T), errs
+
+
+ROUTE = [
+    # the last router in one launch and the first in two (bf16: 96 KB = 24 x 2048)
+    ("one_launch", _cfg(741, 3, 2048, 64, 23, 2), 0),
+    ("two_launches", _cfg(742, 3, 2048, 64, 24, 2), 0),
+    ("two_launches_16", _cfg(743, 16, 1024, 64, 64, 6, S=1), 0),
+    # more than 64 pairs and more than 64 experts, a ragged last expert tile
+    ("many", _cfg(744, 16, 512, 64, 100, 8), 0),
+    ("f32", _cfg(745, 7, 1088, 64, 30, 3, act="f32"), 0),
+    ("f32_one_launch", _cfg(746, 5, 320, 64, 7, 3, act="f32"), 0),
+    # fp32 columns past the last whole pass, ragged token and expert quads
+    ("f32_prefill", _cfg(747, 37, 576, 64, 21, 4, act="f32"), 0),
+    # one token: rank counting (E < 2k) and repeated maxima, at their border
+    ("one_k_of_2k", _cfg(748, 1, 128, 64, 12, 6, S=2), 0),
+    ("one_k_above", _cfg(749, 1, 128, 64, 11, 6), 0),
+    ("one_64", _cfg(750, 1, 256, 64, 64, 16, S=3), 0),
+    ("one_all", _cfg(751, 1, 128, 64, 9, 2, S=1, act="f32"), 1),
+    ("three_all", _cfg(752, 3, 128, 64, 40, 5), 1),
+]
+
+
+@pytest.mark.parametrize("cfg,softmax_all", [pytest.param(c, f, id=i) for i, c, f in ROUTE])
+def test_route_split(mira, cfg, softmax_all):
+    """Routing and output against the oracle, and the one-shot call against the
+    two-phase call (which runs the general kernels) bit for bit."""
+    lay = Layer(cfg)
+    flags = mira.MIRA_FLAG_SOFTMAX_ALL if softmax_all else 0
+    res = lay.run(flags)
+    two = lay.run(flags, two_phase=True, ws_fill=0xFF)
+    for name, v in res.items():
+        assert np.array_equal(v, two[name]), name
+    if not softmax_all:
+        run_and_check(lay, res=res)
+    else:  # the oracle's helper checks renormalised weights; these sum to less
+        lg = res["logits"].astype(np.float64)
+        p = np.exp(lg - lg.max(1, keepdims=True))
+        p /= p.sum(1, keepdims=True)
+        assert np.allclose(res["w"], np.take_along_axis(p, res["idx"].astype(np.int64), 1), rtol=0, atol=2e-6)
