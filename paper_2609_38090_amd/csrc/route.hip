@@ -475,7 +475,7 @@ __device__ __forceinline__ void decode_select(const float* lg, int ld, int T, in
                                               int softmax_all, const ExpertPool& ep,
                                               const PermOut& o, DecodeWork* __restrict__ work,
                                               int max_active, SelectLds& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wave = threadIdx.x >> 6;
   if (one_token_small(T, E, k, S)) {
     // nothing waits after the logits.  Wave 0 selects and writes
     // the descriptors from registers; wave 1 makes the same selection (same

@@ -12,7 +12,7 @@ digits of one-group experts in LDS up to hidden 4096.
 
 Routing: large routers (more than 16 experts and 96 KB of rows) compute their
 logits in a launch of their own; a whole one-token call with at most 64 experts
-selects inside the gate/up kernel."""
+selects inside the gate/up kernel.  Descriptors are ordered by token count."""
 import numpy as np
 import pytest
 
@@ -87,6 +87,11 @@ ROUTE = [
     ("one_k_of_2k", _cfg(748, 1, 128, 64, 12, 6, S=2), 0),
     ("one_k_above", _cfg(749, 1, 128, 64, 11, 6), 0),
     ("one_64", _cfg(750, 1, 256, 64, 64, 16, S=3), 0),
+    # every group size up to T, in both descriptor forms; equal sizes
+    ("sizes", _cfg(753, 16, 128, 64, 20, 3, S=2), 0),
+    ("sizes_many", _cfg(754, 16, 128, 64, 40, 8, S=2), 0),
+    ("sizes_equal", _cfg(755, 16, 128, 64, 8, 8, S=3), 0),
+    ("sizes_254", _cfg(756, 16, 64, 64, 250, 16, S=4), 0),
     ("one_all", _cfg(751, 1, 128, 64, 9, 2, S=1, act="f32"), 1),
     ("three_all", _cfg(752, 3, 128, 64, 40, 5), 1),
 ]
