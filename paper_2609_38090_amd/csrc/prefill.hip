@@ -159,9 +159,20 @@ __device__ __forceinline__ void ring_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Token row r stores its 16-byte chunk c at chunk c ^ tok_swizzle(r).  A
+// 128-bit read serves 16 lanes at a time: lanes 0-3, 12-15 and 20-27 (then
+// 4-11, 16-19 and 28-31) of each half wave, that is rows 0-3 and 12-15 of one
+// k group with rows 4-11 of the next, whose chunk differs in bit 1.  Over the
+// 64 banks (two 128-byte rows) these 16 land on 16 distinct bank groups; with
+// (r >> 1) & 7 alone they fell on 8, and the conflicts were 40% of the LDS
+// cycles of a 4096-token call.
+__device__ __forceinline__ constexpr int tok_swizzle(int r) {
+  const int i = (r >> 1) & 7;
+  return i >= 2 && i < 6 ? i ^ 2 : i;
+}
+
 // Per-lane LDS addresses of one ring slot: the wave's first weight tile and
-// the two token chunks of row r16 (chunk c of row r is stored at chunk
-// c ^ ((r >> 1) & 7)).
+// the two token chunks of row r16.
 struct StageAddr {
   uint32_t w, x0, x1;
 };
@@ -777,8 +788,8 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
   // lane addresses inside a ring slot
   const uint32_t ring_base = lds_addr(ring);
   const uint32_t wl = ring_base + (DUAL ? wave * 4 : wave * kWaveTiles) * 1024 + lane * 16;
-  const uint32_t xl0 = ring_base + r16 * 128 + (((2 * kg) ^ ((r16 >> 1) & 7)) << 4);
-  const uint32_t xl1 = ring_base + r16 * 128 + (((2 * kg + 1) ^ ((r16 >> 1) & 7)) << 4);
+  const uint32_t xl0 = ring_base + r16 * 128 + (((2 * kg) ^ tok_swizzle(r16)) << 4);
+  const uint32_t xl1 = ring_base + r16 * 128 + (((2 * kg + 1) ^ tok_swizzle(r16)) << 4);
   auto slot = [&](int b) {
     const uint32_t o = (uint32_t)b * kStageBytes;
     return StageAddr{wl + o, xl0 + o, xl1 + o};
@@ -905,7 +916,7 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = wave * 32 + i * 8 + (lane >> 3);
-      const int c = (lane & 7) ^ ((r >> 1) & 7);
+      const int c = (lane & 7) ^ tok_swizzle(r);
       xoff[i] = (uint32_t)(((size_t)rows[i] * K + c * 8) * 2);
     }
     // the next tile's token rows load while this tile computes
