@@ -23,15 +23,19 @@
 namespace mira {
 
 constexpr int kGemmThreads = 256;                 // 4 waves, one per SIMD
-constexpr int kWaveTiles = 8;                     // 16-row packed tiles per wave
-constexpr int kTileRows = 4 * kWaveTiles * 16;    // 512 weight rows per workgroup tile
 constexpr int kNStage = 3;                        // LDS ring: two stages in flight
-constexpr int kWStage = kTileRows * 64;           // 32 KB of packed tiles per stage
 constexpr int kXStage = kPrefBM * 64 * 2;         // 16 KB of tokens (128 x 64 bf16)
-constexpr int kStageBytes = kWStage + kXStage;    // 48 KB
-constexpr int kDmaPerStage = 12;                  // loads per wave and stage: 8 tiles, 4 row groups
 static_assert(kPrefBM == 128, "the token stage holds 128 rows");
-static_assert(kNStage * kStageBytes <= 160 * 1024, "LDS ring exceeds 160 KB");
+
+// Tile shapes, by the 16-row packed tiles WT of a wave: 8 (512 weight rows
+// per workgroup tile), or 2 for a down GEMM whose 512-row tiles would leave
+// more than half of the CUs idle.
+constexpr int kWideTiles = 8, kNarrowTiles = 2;
+__host__ __device__ constexpr int tile_rows(int WT) { return 4 * WT * 16; }
+constexpr int wstage_bytes(int WT) { return tile_rows(WT) * 64; }  // packed tiles per stage (WT 8: 32 KB)
+constexpr int stage_bytes(int WT) { return wstage_bytes(WT) + kXStage; }
+constexpr int dma_per_stage(int WT) { return WT + 4; }  // loads per wave and stage: tiles, then row groups
+static_assert(kNStage * stage_bytes(kWideTiles) <= 160 * 1024, "LDS ring exceeds 160 KB");
 
 // 16 int8 -> two groups of 8 bf16.  int8 -> fp32 is exact and an integer of
 // magnitude <= 127 has a zero low half-word in fp32, so its bf16 is the
@@ -119,7 +123,14 @@ struct Frag {
 // Wait until at most N LDS reads are outstanding; the fragment registers are
 // tied so no use of them moves above the wait.
 template <int N, int MS>
-__device__ __forceinline__ void lgkm_wait_all(Frag<MS>& f, v4i (&q)[kWaveTiles]) {
+__device__ __forceinline__ void lgkm_wait_all(Frag<MS>& f, v4i (&q)[kNarrowTiles]) {
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(N));
+#pragma unroll
+  for (int ms = 0; ms < MS; ++ms) asm volatile("" : "+v"(f.bx[ms][0]), "+v"(f.bx[ms][1]));
+  asm volatile("" : "+v"(q[0]), "+v"(q[1]));
+}
+template <int N, int MS>
+__device__ __forceinline__ void lgkm_wait_all(Frag<MS>& f, v4i (&q)[kWideTiles]) {
   if constexpr (MS == 8) {
     asm volatile("s_waitcnt lgkmcnt(%24)"
                  : "+v"(f.bx[0][0]), "+v"(f.bx[0][1]), "+v"(f.bx[1][0]), "+v"(f.bx[1][1]),
@@ -195,8 +206,7 @@ __device__ __forceinline__ constexpr int wtile_off(int j) {
 // nlo/nhi; the accumulation chains are back-to-back MFMAs (interlocked).
 constexpr uint32_t kPermHi16 = 0x07060302u;  // v_perm: upper half-words of two fp32
 
-template <int J>
-__device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][8], const Frag<8>& cur, v4i alo,
+__device__ __forceinline__ void mfma_chunk(v4f (&acc)[8], const Frag<8>& cur, v4i alo,
                                            v4i ahi, v4i qn, v4i& nlo, v4i& nhi,
                                            const Dma (&d)[2]) {
   uint32_t o[8], t0, t1;
@@ -248,8 +258,8 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][8], const Frag<8>& cur,
       "v_mfma_f32_16x16x32_bf16 %5, %35, %29, %5\n"
       "v_mfma_f32_16x16x32_bf16 %6, %35, %31, %6\n"
       "v_mfma_f32_16x16x32_bf16 %7, %35, %33, %7\n"
-      : "+a"(acc[J][0]), "+a"(acc[J][1]), "+a"(acc[J][2]), "+a"(acc[J][3]), "+a"(acc[J][4]),
-        "+a"(acc[J][5]), "+a"(acc[J][6]), "+a"(acc[J][7]), "=&v"(o[0]), "=&v"(o[1]),
+      : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]), "+a"(acc[4]),
+        "+a"(acc[5]), "+a"(acc[6]), "+a"(acc[7]), "=&v"(o[0]), "=&v"(o[1]),
         "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7]), "=&v"(t0),
         "=&v"(t1)
       : "v"(cur.bx[0][0]), "v"(cur.bx[0][1]), "v"(cur.bx[1][0]), "v"(cur.bx[1][1]),
@@ -264,8 +274,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][8], const Frag<8>& cur,
   nhi = v4i{(int)o[4], (int)o[5], (int)o[6], (int)o[7]};
 }
 
-template <int J>
-__device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][8], const Frag<8>& cur, v4i alo,
+__device__ __forceinline__ void mfma_chunk(v4f (&acc)[8], const Frag<8>& cur, v4i alo,
                                            v4i ahi, v4i qn, v4i& nlo, v4i& nhi,
                                            const Dma (&d)[1]) {
   uint32_t o[8], t0, t1;
@@ -314,8 +323,8 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][8], const Frag<8>& cur,
       "v_mfma_f32_16x16x32_bf16 %5, %35, %29, %5\n"
       "v_mfma_f32_16x16x32_bf16 %6, %35, %31, %6\n"
       "v_mfma_f32_16x16x32_bf16 %7, %35, %33, %7\n"
-      : "+a"(acc[J][0]), "+a"(acc[J][1]), "+a"(acc[J][2]), "+a"(acc[J][3]), "+a"(acc[J][4]),
-        "+a"(acc[J][5]), "+a"(acc[J][6]), "+a"(acc[J][7]), "=&v"(o[0]), "=&v"(o[1]),
+      : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]), "+a"(acc[4]),
+        "+a"(acc[5]), "+a"(acc[6]), "+a"(acc[7]), "=&v"(o[0]), "=&v"(o[1]),
         "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7]), "=&v"(t0),
         "=&v"(t1)
       : "v"(cur.bx[0][0]), "v"(cur.bx[0][1]), "v"(cur.bx[1][0]), "v"(cur.bx[1][1]),
@@ -329,8 +338,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][8], const Frag<8>& cur,
   nhi = v4i{(int)o[4], (int)o[5], (int)o[6], (int)o[7]};
 }
 
-template <int J>
-__device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][4], const Frag<4>& cur, v4i alo,
+__device__ __forceinline__ void mfma_chunk(v4f (&acc)[4], const Frag<4>& cur, v4i alo,
                                            v4i ahi, v4i qn, v4i& nlo, v4i& nhi,
                                            const Dma (&d)[2]) {
   uint32_t o[8], t0, t1;
@@ -374,7 +382,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][4], const Frag<4>& cur,
       "v_perm_b32 %11, %13, %12, %28\n"
       "v_mfma_f32_16x16x32_bf16 %2, %23, %19, %2\n"
       "v_mfma_f32_16x16x32_bf16 %3, %23, %21, %3\n"
-      : "+a"(acc[J][0]), "+a"(acc[J][1]), "+a"(acc[J][2]), "+a"(acc[J][3]), "=&v"(o[0]),
+      : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]), "=&v"(o[0]),
         "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]),
         "=&v"(o[7]), "=&v"(t0), "=&v"(t1)
       : "v"(cur.bx[0][0]), "v"(cur.bx[0][1]), "v"(cur.bx[1][0]), "v"(cur.bx[1][1]),
@@ -387,8 +395,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][4], const Frag<4>& cur,
   nhi = v4i{(int)o[4], (int)o[5], (int)o[6], (int)o[7]};
 }
 
-template <int J>
-__device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][4], const Frag<4>& cur, v4i alo,
+__device__ __forceinline__ void mfma_chunk(v4f (&acc)[4], const Frag<4>& cur, v4i alo,
                                            v4i ahi, v4i qn, v4i& nlo, v4i& nhi,
                                            const Dma (&d)[1]) {
   uint32_t o[8], t0, t1;
@@ -429,7 +436,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][4], const Frag<4>& cur,
       "v_perm_b32 %11, %13, %12, %28\n"
       "v_mfma_f32_16x16x32_bf16 %2, %23, %19, %2\n"
       "v_mfma_f32_16x16x32_bf16 %3, %23, %21, %3\n"
-      : "+a"(acc[J][0]), "+a"(acc[J][1]), "+a"(acc[J][2]), "+a"(acc[J][3]), "=&v"(o[0]),
+      : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]), "=&v"(o[0]),
         "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]),
         "=&v"(o[7]), "=&v"(t0), "=&v"(t1)
       : "v"(cur.bx[0][0]), "v"(cur.bx[0][1]), "v"(cur.bx[1][0]), "v"(cur.bx[1][1]),
@@ -441,8 +448,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][4], const Frag<4>& cur,
   nhi = v4i{(int)o[4], (int)o[5], (int)o[6], (int)o[7]};
 }
 
-template <int J>
-__device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][2], const Frag<2>& cur, v4i alo,
+__device__ __forceinline__ void mfma_chunk(v4f (&acc)[2], const Frag<2>& cur, v4i alo,
                                            v4i ahi, v4i qn, v4i& nlo, v4i& nhi,
                                            const Dma (&d)[2]) {
   uint32_t o[8], t0, t1;
@@ -482,7 +488,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][2], const Frag<2>& cur,
       "s_nop 0\n"
       "global_load_lds_dwordx4 %26, %27\n"
       "v_mfma_f32_16x16x32_bf16 %1, %17, %15, %1\n"
-      : "+a"(acc[J][0]), "+a"(acc[J][1]), "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]),
+      : "+a"(acc[0]), "+a"(acc[1]), "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]),
         "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7]), "=&v"(t0), "=&v"(t1)
       : "v"(cur.bx[0][0]), "v"(cur.bx[0][1]), "v"(cur.bx[1][0]), "v"(cur.bx[1][1]), "v"(alo),
         "v"(ahi), "v"(qn[0]), "v"(qn[1]), "v"(qn[2]), "v"(qn[3]), "s"(kPermHi16),
@@ -493,8 +499,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][2], const Frag<2>& cur,
   nhi = v4i{(int)o[4], (int)o[5], (int)o[6], (int)o[7]};
 }
 
-template <int J>
-__device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][2], const Frag<2>& cur, v4i alo,
+__device__ __forceinline__ void mfma_chunk(v4f (&acc)[2], const Frag<2>& cur, v4i alo,
                                            v4i ahi, v4i qn, v4i& nlo, v4i& nhi,
                                            const Dma (&d)[1]) {
   uint32_t o[8], t0, t1;
@@ -531,7 +536,7 @@ __device__ __forceinline__ void mfma_chunk(v4f (&acc)[8][2], const Frag<2>& cur,
       "v_perm_b32 %9, %11, %10, %22\n"
       "v_mfma_f32_16x16x32_bf16 %0, %17, %13, %0\n"
       "v_mfma_f32_16x16x32_bf16 %1, %17, %15, %1\n"
-      : "+a"(acc[J][0]), "+a"(acc[J][1]), "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]),
+      : "+a"(acc[0]), "+a"(acc[1]), "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]),
         "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7]), "=&v"(t0), "=&v"(t1)
       : "v"(cur.bx[0][0]), "v"(cur.bx[0][1]), "v"(cur.bx[1][0]), "v"(cur.bx[1][1]), "v"(alo),
         "v"(ahi), "v"(qn[0]), "v"(qn[1]), "v"(qn[2]), "v"(qn[3]), "s"(kPermHi16),
@@ -583,13 +588,21 @@ __device__ __forceinline__ void mfma_drain(v4f (&acc)[8][2]) {
                  "+a"(acc[6][0]), "+a"(acc[6][1]), "+a"(acc[7][0]), "+a"(acc[7][1]));
 }
 
+__device__ __forceinline__ void mfma_drain(v4f (&acc)[kNarrowTiles][8]) {
+  asm volatile("s_nop 7\n s_nop 7\n s_nop 7\n"
+               : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
+                 "+a"(acc[0][4]), "+a"(acc[0][5]), "+a"(acc[0][6]), "+a"(acc[0][7]),
+                 "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]),
+                 "+a"(acc[1][4]), "+a"(acc[1][5]), "+a"(acc[1][6]), "+a"(acc[1][7]));
+}
+
 #pragma clang diagnostic pop
 
 // Token-fragment read I (of 2*MS) of a stage.
-template <int MS, int I>
+template <int WT, int MS, int I>
 __device__ __forceinline__ void read_bx(Frag<MS>& f, const StageAddr& a) {
-  if constexpr (I & 1) f.bx[I >> 1][1] = lds_read128<kWStage + (I >> 1) * 2048>(a.x1);
-  else f.bx[I >> 1][0] = lds_read128<kWStage + (I >> 1) * 2048>(a.x0);
+  if constexpr (I & 1) f.bx[I >> 1][1] = lds_read128<wstage_bytes(WT) + (I >> 1) * 2048>(a.x1);
+  else f.bx[I >> 1][0] = lds_read128<wstage_bytes(WT) + (I >> 1) * 2048>(a.x0);
 }
 
 // One stage.  On entry: cur holds this stage's token fragments, q[1..7] this
@@ -598,31 +611,35 @@ __device__ __forceinline__ void read_bx(Frag<MS>& f, const StageAddr& a) {
 // into q[j] (free since its widening in chunk j-1) and a share of its token
 // fragments into nxt, and issues a share of the refill dma(j, i).  On exit
 // c0lo/c0hi hold the next stage's widened tile 0.
-template <bool DUAL, int MS, typename DmaFn>
-__device__ __forceinline__ void stage_body(v4f (&acc)[kWaveTiles][MS], const Frag<MS>& cur,
-                                           Frag<MS>& nxt, v4i (&q)[kWaveTiles],
+template <bool DUAL, int WT, int MS, typename DmaFn>
+__device__ __forceinline__ void stage_body(v4f (&acc)[WT][MS], const Frag<MS>& cur,
+                                           Frag<MS>& nxt, v4i (&q)[WT],
                                            const StageAddr& a, v4i& c0lo, v4i& c0hi,
                                            DmaFn dma) {
   constexpr int NB = 2 * MS;  // token-fragment reads per stage
   v4i lo = c0lo, hi = c0hi;
-  static_for<0, kWaveTiles>([&](auto jc) {
+  static_for<0, WT>([&](auto jc) {
     constexpr int J = jc;
-    constexpr int b0 = J * NB / kWaveTiles, b1 = (J + 1) * NB / kWaveTiles;
-    if constexpr (J == kWaveTiles - 1) {
+    constexpr int b0 = J * NB / WT, b1 = (J + 1) * NB / WT;
+    if constexpr (J == WT - 1) {
       // the next stage's tile 0, the first read of this stage, has landed
-      constexpr int before = (kWaveTiles - 1) + (J * NB / kWaveTiles);
+      constexpr int before = (WT - 1) + (J * NB / WT);
       lgkm_wait_one<(before - 1 < 15 ? before - 1 : 15)>(q[0]);
     }
+    const v4i qn = J + 1 < WT ? q[(J + 1) % WT] : q[0];
     q[J] = lds_read128<wtile_off<DUAL>(J)>(a.w);
-    static_for<b0, b1>([&](auto i) { read_bx<MS, i>(nxt, a); });
+    static_for<b0, b1>([&](auto i) { read_bx<WT, MS, i>(nxt, a); });
     v4i nlo, nhi;
-    const v4i qn = J + 1 < kWaveTiles ? q[(J + 1) % kWaveTiles] : q[0];
-    if constexpr (J < 4) {
+    if constexpr (WT == kNarrowTiles) {
+      dma16(dma(3 * J));
+      const Dma d[2] = {dma(3 * J + 1), dma(3 * J + 2)};
+      mfma_chunk(acc[J], cur, lo, hi, qn, nlo, nhi, d);
+    } else if constexpr (J < 4) {
       const Dma d[2] = {dma(2 * J), dma(2 * J + 1)};
-      mfma_chunk<J>(acc, cur, lo, hi, qn, nlo, nhi, d);
+      mfma_chunk(acc[J], cur, lo, hi, qn, nlo, nhi, d);
     } else {
       const Dma d[1] = {dma(4 + J)};
-      mfma_chunk<J>(acc, cur, lo, hi, qn, nlo, nhi, d);
+      mfma_chunk(acc[J], cur, lo, hi, qn, nlo, nhi, d);
     }
     lo = nlo;
     hi = nhi;
@@ -632,37 +649,38 @@ __device__ __forceinline__ void stage_body(v4f (&acc)[kWaveTiles][MS], const Fra
 }
 
 // Wait until at most n whole stages of this wave's loads are in flight.
+template <int WT>
 __device__ __forceinline__ void wait_stages(int n) {
-  static_assert(kNStage <= 4 && kDmaPerStage * (kNStage - 1) < 64, "vmcnt immediates");
-  if (n >= 2) wait_vmcnt<2 * kDmaPerStage>();
-  else if (n == 1) wait_vmcnt<kDmaPerStage>();
+  static_assert(kNStage <= 4 && dma_per_stage(WT) * (kNStage - 1) < 64, "vmcnt immediates");
+  if (n >= 2) wait_vmcnt<2 * dma_per_stage(WT)>();
+  else if (n == 1) wait_vmcnt<dma_per_stage(WT)>();
   else wait_vmcnt<0>();
 }
 
 // The k loop of one tile over nst stages.  dma(s, i) describes load i (of
-// kDmaPerStage) of stage s into ring slot s % kNStage; slot(b) gives the lane
+// dma_per_stage) of stage s into ring slot s % kNStage; slot(b) gives the lane
 // addresses of ring slot b.
-template <bool DUAL, int MS, typename DmaFn, typename Slot>
-__device__ __forceinline__ void tile_kloop(v4f (&acc)[kWaveTiles][MS], int nst, DmaFn dma,
+template <bool DUAL, int WT, int MS, typename DmaFn, typename Slot>
+__device__ __forceinline__ void tile_kloop(v4f (&acc)[WT][MS], int nst, DmaFn dma,
                                            Slot slot) {
 #pragma unroll
-  for (int j = 0; j < kWaveTiles; ++j)
+  for (int j = 0; j < WT; ++j)
 #pragma unroll
     for (int ms = 0; ms < MS; ++ms) acc[j][ms] = v4f{0.f, 0.f, 0.f, 0.f};
 
   const int pre = nst < kNStage ? nst : kNStage;
   for (int s = 0; s < pre; ++s)
-    for (int i = 0; i < kDmaPerStage; ++i) dma16(dma(s, i));
-  wait_stages(pre - 1);
+    for (int i = 0; i < dma_per_stage(WT); ++i) dma16(dma(s, i));
+  wait_stages<WT>(pre - 1);
   ring_barrier();  // stage 0 is in LDS for every wave
 
   Frag<MS> fa, fb;
-  v4i q[kWaveTiles];
+  v4i q[WT];
   v4i c0lo, c0hi;
   {
     const StageAddr a = slot(0);
-    static_for<0, kWaveTiles>([&](auto j) { q[j] = lds_read128<wtile_off<DUAL>(j)>(a.w); });
-    static_for<0, 2 * MS>([&](auto i) { read_bx<MS, i>(fa, a); });
+    static_for<0, WT>([&](auto j) { q[j] = lds_read128<wtile_off<DUAL>(j)>(a.w); });
+    static_for<0, 2 * MS>([&](auto i) { read_bx<WT, MS, i>(fa, a); });
   }
   lgkm_wait_all<0>(fa, q);
   i8x16_to_bf16(q[0], c0lo, c0hi);
@@ -673,12 +691,12 @@ __device__ __forceinline__ void tile_kloop(v4f (&acc)[kWaveTiles][MS], int nst, 
   int slot_next = 1 % kNStage;
   auto step = [&](int s, Frag<MS>& cur, Frag<MS>& nxt) {
     lgkm_wait_all<0>(cur, q);
-    wait_stages(pre - 2);  // one refill per step: stage s+1 has pre-2 refills behind it
+    wait_stages<WT>(pre - 2);  // one refill per step: stage s+1 has pre-2 refills behind it
     ring_barrier();
     // past the end of the tile the slot is reloaded with its own stage s (a
     // harmless copy), which keeps one code path and a fixed queue depth
     const int sn = s + kNStage < nst ? s + kNStage : s;
-    stage_body<DUAL, MS>(acc, cur, nxt, q, slot(slot_next), c0lo, c0hi,
+    stage_body<DUAL, WT, MS>(acc, cur, nxt, q, slot(slot_next), c0lo, c0hi,
                          [&](int i) { return dma(sn, i); });
     slot_next = slot_next + 1 == kNStage ? 0 : slot_next + 1;
   };
@@ -698,8 +716,8 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.f + e) * u;
 }
 
-template <bool DUAL, int MS>
-__device__ __forceinline__ void tile_epilogue(const v4f (&acc)[kWaveTiles][MS], int wave,
+template <bool DUAL, int WT, int MS>
+__device__ __forceinline__ void tile_epilogue(const v4f (&acc)[WT][MS], int wave,
                                               int lane, int n0, int N, int R, int C, int p0,
                                               int nv, const int8_t* blob, uint16_t* hout,
                                               uint16_t* hout_lo, float* ybase) {
@@ -745,8 +763,8 @@ __device__ __forceinline__ void tile_epilogue(const v4f (&acc)[kWaveTiles][MS], 
     }
   } else {
 #pragma unroll
-    for (int j = 0; j < kWaveTiles; ++j) {
-      const int cc = n0 + (wave * kWaveTiles + j) * 16 + kg * 4;
+    for (int j = 0; j < WT; ++j) {
+      const int cc = n0 + (wave * WT + j) * 16 + kg * 4;
       if (cc >= N) continue;
 #pragma unroll
       for (int ms = 0; ms < MS; ++ms) {
@@ -763,7 +781,7 @@ __device__ __forceinline__ void tile_epilogue(const v4f (&acc)[kWaveTiles][MS], 
 // tile runs its k range twice, over act and then over act_lo with the same
 // weights, into the same accumulators.  hout_lo (gate/up, may be null)
 // receives the low bf16 parts of H' for the down GEMM's second pass.
-template <bool DUAL>
+template <bool DUAL, int WT>
 __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     int C, int R, int G, int KSmax, ExpertPool ep, int32_t* __restrict__ misc,
     const int32_t* __restrict__ offsets,
@@ -774,11 +792,12 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
   // each), then 128 token rows x 64 bf16 with the 16-byte chunk c of row r at
   // chunk c ^ ((r >> 1) & 7): the 64 banks span two 128-byte rows, so the 16
   // rows of one read phase land on 16 distinct 16-byte bank groups.
-  __shared__ __attribute__((aligned(1024))) int8_t ring[kNStage * kStageBytes];
+  __shared__ __attribute__((aligned(1024))) int8_t ring[kNStage * stage_bytes(WT)];
 
   const int K = DUAL ? C : R;   // contraction length
   const int N = DUAL ? R : C;   // weight rows per matrix
-  const int rows_per_mat = DUAL ? kTileRows / 2 : kTileRows;
+  static_assert(!DUAL || WT == kWideTiles, "the gate/up tile halves are 16 packed tiles");
+  const int rows_per_mat = DUAL ? tile_rows(WT) / 2 : tile_rows(WT);
   const int NT = (N + rows_per_mat - 1) / rows_per_mat;
   const int nks = K / 64;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -787,17 +806,17 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
 
   // lane addresses inside a ring slot
   const uint32_t ring_base = lds_addr(ring);
-  const uint32_t wl = ring_base + (DUAL ? wave * 4 : wave * kWaveTiles) * 1024 + lane * 16;
+  const uint32_t wl = ring_base + (DUAL ? wave * 4 : wave * WT) * 1024 + lane * 16;
   const uint32_t xl0 = ring_base + r16 * 128 + (((2 * kg) ^ tok_swizzle(r16)) << 4);
   const uint32_t xl1 = ring_base + r16 * 128 + (((2 * kg + 1) ^ tok_swizzle(r16)) << 4);
   auto slot = [&](int b) {
-    const uint32_t o = (uint32_t)b * kStageBytes;
+    const uint32_t o = (uint32_t)b * stage_bytes(WT);
     return StageAddr{wl + o, xl0 + o, xl1 + o};
   };
   // LDS destinations of this wave's loads: packed tiles 8w..8w+7 and token
   // rows 32w..32w+31 of a slot
-  const uint32_t m0_w = ring_base + wave * kWaveTiles * 1024;
-  const uint32_t m0_x = ring_base + kWStage + wave * 32 * 128;
+  const uint32_t m0_w = ring_base + wave * WT * 1024;
+  const uint32_t m0_x = ring_base + wstage_bytes(WT) + wave * 32 * 128;
 
   // group tables in LDS (offsets, slots and the prefix of m-tiles of kPrefBM
   // positions over groups); the tile walk below reads them for every tile
@@ -904,10 +923,10 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     // 4 groups of 8 token rows per stage, as 32-bit lane offsets from a
     // scalar base that advances by one stage.  Rows past the matrix read a
     // valid row instead (their products are never stored).
-    uint32_t woff[kWaveTiles], xoff[4];
+    uint32_t woff[WT], xoff[4];
 #pragma unroll
-    for (int i = 0; i < kWaveTiles; ++i) {
-      const int tl = wave * kWaveTiles + i;
+    for (int i = 0; i < WT; ++i) {
+      const int tl = wave * WT + i;
       const int mat = DUAL ? (tl >> 4) : 0, rt = DUAL ? (tl & 15) : tl;
       const int row = n0 + rt * 16;
       woff[i] = (uint32_t)((size_t)mat * R * C + (size_t)((row < N ? row : n0) >> 4) * nks * 1024) +
@@ -927,7 +946,7 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
       // out.  Its H' rows stay unwritten; only this GEMM would read them.
       if (!DUAL) {
         float* yb = yout + (size_t)t.split * ysplit;
-        const int q4 = min(kTileRows, N - n0) / 4;
+        const int q4 = min(tile_rows(WT), N - n0) / 4;
         for (int i = tid; i < nv * q4; i += kGemmThreads)
           *(v4f*)(yb + (size_t)(p0 + i / q4) * C + n0 + (i % q4) * 4) = v4f{0.f, 0.f, 0.f, 0.f};
       }
@@ -940,11 +959,11 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     // load i of stage s: packed tiles for i < 8, token row groups after;
     // stages nst .. 2*nst-1 (two-pass calls) repeat the weights over act_lo
     auto dma = [&](int s, int i) {
-      const uint32_t so = (uint32_t)(s % kNStage) * kStageBytes;
+      const uint32_t so = (uint32_t)(s % kNStage) * stage_bytes(WT);
       const bool lo = s >= nst;
       const int sk = lo ? s - nst : s;
-      if (i < kWaveTiles) return Dma{woff[i], wstage0 + (size_t)sk * 1024, m0_w + so + i * 1024};
-      const int r = i - kWaveTiles;
+      if (i < WT) return Dma{woff[i], wstage0 + (size_t)sk * 1024, m0_w + so + i * 1024};
+      const int r = i - WT;
       return Dma{xoff[r], (lo ? xstage0_lo : xstage0) + (size_t)sk * 128, m0_x + so + r * 1024};
     };
     const int nst_all = act_lo ? 2 * nst : nst;
@@ -956,20 +975,21 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     ring_barrier();
 
     float* ybase = DUAL ? nullptr : yout + (size_t)t.split * ysplit;
+    auto run = [&](auto ms) {
+      constexpr int MS = ms;
+      v4f acc[WT][MS];
+      tile_kloop<DUAL, WT, MS>(acc, nst_all, dma, slot);
+      tile_epilogue<DUAL, WT, MS>(acc, wave, lane, n0, N, R, C, p0, nv, blob, hout, hout_lo, ybase);
+    };
     // token subtiles actually present: the group's last tile runs a shorter
-    // loop when it holds at most 64 or 32 tokens
-    if (nv > 64) {
-      v4f acc[kWaveTiles][8];
-      tile_kloop<DUAL, 8>(acc, nst_all, dma, slot);
-      tile_epilogue<DUAL, 8>(acc, wave, lane, n0, N, R, C, p0, nv, blob, hout, hout_lo, ybase);
-    } else if (nv > 32) {
-      v4f acc[kWaveTiles][4];
-      tile_kloop<DUAL, 4>(acc, nst_all, dma, slot);
-      tile_epilogue<DUAL, 4>(acc, wave, lane, n0, N, R, C, p0, nv, blob, hout, hout_lo, ybase);
+    // loop when it holds at most 64 or 32 tokens (a narrow tile's stage has 32
+    // MFMAs and waits for its loads either way)
+    if constexpr (WT == kNarrowTiles) {
+      run(std::integral_constant<int, 8>{});
     } else {
-      v4f acc[kWaveTiles][2];
-      tile_kloop<DUAL, 2>(acc, nst_all, dma, slot);
-      tile_epilogue<DUAL, 2>(acc, wave, lane, n0, N, R, C, p0, nv, blob, hout, hout_lo, ybase);
+      if (nv > 64) run(std::integral_constant<int, 8>{});
+      else if (nv > 32) run(std::integral_constant<int, 4>{});
+      else run(std::integral_constant<int, 2>{});
     }
   }
 }
@@ -1049,24 +1069,34 @@ hipError_t launch_prefill(const mira_shape& s, const Layout& L, const WsPtr& w, 
   }
   const size_t ysplit = (size_t)L.P * L.C;
   {
-    auto kern = prefill_gemm_kernel<true>;
+    auto kern = prefill_gemm_kernel<true, kWideTiles>;
     static std::once_flag once;
     static int occ = 0;
-    const long tiles = (long)L.mt_max * ((L.R + kTileRows / 2 - 1) / (kTileRows / 2));
+    const long tiles = (long)L.mt_max * ((L.R + tile_rows(kWideTiles) / 2 - 1) / (tile_rows(kWideTiles) / 2));
     const int grid = persistent_grid(gemm_occupancy(kern, once, occ), tiles);
     launch_timed("prefill_gateup", kern, dim3(grid), dim3(kGemmThreads), 0, st, L.C, L.R, L.G, 1,
                  ep, w.misc, w.offsets, w.tokpos, xb, xlo, w.hbuf, hlo, (float*)nullptr, (size_t)0);
   }
-  {
-    auto kern = prefill_gemm_kernel<false>;
+  // Down in tiles of 512 rows, or of 128 where even the upper bound of 512-row
+  // tiles (k-chunks included) would leave more than half of the CUs without
+  // one: a narrow tile's token stages are read by four times the workgroups,
+  // but the chain of stages runs four times as wide.  301 fp32 tokens, C 1024,
+  // R 2816, 16 + 1 experts (about 40 wide tiles): the layer call took 195 us
+  // with wide tiles and takes 132 us.
+  const auto down = [&](auto wt) {
+    constexpr int WT = wt;
+    auto kern = prefill_gemm_kernel<false, WT>;
     static std::once_flag once;
     static int occ = 0;
-    const long tiles = (long)L.mt_max * ((L.C + kTileRows - 1) / kTileRows) * L.ksplit;
+    const long tiles = (long)L.mt_max * ((L.C + tile_rows(WT) - 1) / tile_rows(WT)) * L.ksplit;
     const int grid = persistent_grid(gemm_occupancy(kern, once, occ), tiles);
     launch_timed("prefill_down", kern, dim3(grid), dim3(kGemmThreads), 0, st, L.C, L.R, L.G,
                  L.ksplit, ep, w.misc, w.offsets, w.tokpos, (const uint16_t*)w.hbuf,
                  (const uint16_t*)hlo, (uint16_t*)nullptr, (uint16_t*)nullptr, w.ybuf, ysplit);
-  }
+  };
+  const long wide = (long)L.mt_max * ((L.C + tile_rows(kWideTiles) - 1) / tile_rows(kWideTiles)) * L.ksplit;
+  if (2 * wide <= device_cu_count()) down(std::integral_constant<int, kNarrowTiles>{});
+  else down(std::integral_constant<int, kWideTiles>{});
   {
     dim3 grid((L.C / 4 + 255) / 256, T);
     launch_timed("prefill_combine", combine_kernel, grid, dim3(256), 0, st, T, L.C, L.k, L.S,
