@@ -533,9 +533,11 @@ __global__ __launch_bounds__(64 * KS) void decode_down_kernel(
       n_act += __popcll(__ballot(a < max_active && work[a < max_active ? a : 0].group >= 0));
     }
     const int total = n_act * nks;
-    // even for INT4, whose loads cover two k-steps (nks is even there)
-    const int per = I4 ? (((total + KS - 1) / KS + 1) & ~1) : (total + KS - 1) / KS;
-    const int u0 = wave * per, u1 = min(total, u0 + per);
+    // the waves of all gridDim.y workgroups of this row tile; even for INT4,
+    // whose loads cover two k-steps (nks is even there)
+    const int nw = KS * gridDim.y;
+    const int per = I4 ? (((total + nw - 1) / nw + 1) & ~1) : (total + nw - 1) / nw;
+    const int u0 = (blockIdx.y * KS + wave) * per, u1 = min(total, u0 + per);
     if (u0 < u1) {
       int a = u0 / nks;
       int slot = work[a].slot, off = work[a].off, n = work[a].n;
@@ -571,8 +573,18 @@ __global__ __launch_bounds__(64 * KS) void decode_down_kernel(
     float s = 0.f;
 #pragma unroll
     for (int w = 0; w < KS; ++w) s += part[w][t][r];
-    out[(size_t)t * C + blockIdx.x * 16 + r] = s;
+    out[((size_t)blockIdx.y * T + t) * C + blockIdx.x * 16 + r] = s;
   }
+}
+
+// out = sum over p < parts of part[p], in order; n floats each, n a multiple of 4
+__global__ __launch_bounds__(256) void decode_add_kernel(const float* __restrict__ part, int parts,
+                                                         float* __restrict__ out, int n) {
+  const int i = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= n) return;
+  v4f s = *(const v4f*)(part + i);
+  for (int p = 1; p < parts; ++p) s += *(const v4f*)(part + (size_t)p * n + i);
+  *(v4f*)(out + i) = s;
 }
 
 // Waves per workgroup: 16 for INT8 (twice the loads in flight per CU of 8
@@ -595,10 +607,38 @@ constexpr int down_waves() { return I4 ? 14 : 16; }
 // expert fills two batches of a wave, 1% behind with one token.
 constexpr int kDownFlatSteps = 96;
 
+// How many workgroups share each 16-row tile, an equal part of the
+// concatenated k-steps each: as many (up to 4) as the CUs that the C/16 tiles
+// leave idle allow, with at least kDownPartSteps steps (of the experts the call
+// can reach) a part, so that they outlast the launch that adds the partial
+// outputs (some 4 us).  Those lie in the prefill path's partials, which decode
+// calls do not use.  us per call with 1 / 2 workgroups a tile: C 2048, R 1408,
+// 64 experts top-6, 2 shared: 2 tokens (308 steps) 34.7 / 33.8, 8 tokens 57.8 /
+// 53.4, 16 tokens 89.5 / 82.4 (INT4 33.4 / 33.3, 50.3 / 47.7, 75.5 / 71.2); with 1 / 2 / 4: C
+// 512, R 2816, 64 experts top-4: 2 tokens 30.6 / 29.0 / - , 8 tokens 43.0 /
+// 38.0 / 33.8, 16 tokens 66.3 / 56.9 / 49.6.  Below 300 steps it is even.
+constexpr int kDownPartSteps = 150, kDownMaxParts = 4;
+static int down_parts(const Layout& L, const float* out) {
+  if (L.T == 1 || L.R / 64 > kDownFlatSteps || (uintptr_t)out % 16 != 0) return 1;
+  int parts = std::min(kDownMaxParts, device_cu_count() / (L.C / 16));
+  parts = std::min(parts, decode_max_active(L) * (L.R / 64) / kDownPartSteps);
+  parts = std::min(parts, L.ksplit * L.P / L.T);
+  return std::max(parts, 1);
+}
+
 template <int NG, bool I4, int HD, bool TE = false>
 static void launch_decode_down_ng(const Layout& L, const WsPtr& w, const ExpertPool& ep,
                                   float* out, hipStream_t st) {
   constexpr int KS = down_waves<I4>();
+  const int parts = down_parts(L, out);
+  if (parts > 1) {
+    launch_timed("decode_down", (decode_down_kernel<NG, KS, I4, HD, TE, true>), dim3(L.C / 16, parts),
+                 dim3(64 * KS), 0, st, L.C, L.R, L.T, decode_max_active(L), ep, w.dwork, w.hdig, w.hexp, w.ybuf);
+    const int n = L.T * L.C;
+    launch_timed("decode_add", decode_add_kernel, dim3((n / 4 + 255) / 256), dim3(256), 0, st,
+                 (const float*)w.ybuf, parts, out, n);
+    return;
+  }
   const auto kern = L.R / 64 <= kDownFlatSteps ? decode_down_kernel<NG, KS, I4, HD, TE, true>
                                                : decode_down_kernel<NG, KS, I4, HD, TE, false>;
   launch_timed("decode_down", kern, dim3(L.C / 16), dim3(64 * KS), 0, st, L.C, L.R, L.T,

@@ -39,6 +39,15 @@ DOWN = [
     ("first_split", _cfg(706, 9, 64, 6208, 4, 2), "int8"),
     ("last_flat_one", _cfg(707, 1, 64, 6144, 4, 2), "int8"),
     ("first_split_int4", _cfg(708, 6, 128, 6272, 4, 2), "int4"),
+    # several workgroups per row tile, one per 150 k-steps (experts reachable *
+    # R/64), as the CUs allow: the last whole tile, the first shared by two, by
+    # four (more waves than some hold steps), two at the largest hidden size
+    ("last_whole", _cfg(710, 2, 64, 1344, 64, 6, S=2), "int8"),
+    ("first_shared", _cfg(711, 2, 64, 1408, 64, 6, S=2), "int8"),
+    ("shared_by_4_int4", _cfg(712, 16, 128, 640, 64, 6, S=2), "int4"),
+    ("shared_by_4", _cfg(715, 11, 192, 768, 64, 6, S=1, act="f32"), "int8"),
+    ("shared_2048", _cfg(713, 2, 2048, 6144, 16, 4, act="f32"), "int8"),
+    ("whole_2112", _cfg(714, 2, 2112, 6144, 16, 4), "int8"),
     # runs that start and end inside experts
     ("ragged_runs", _cfg(709, 5, 192, 832, 7, 3, S=1, act="f32"), "int8"),
 ]
