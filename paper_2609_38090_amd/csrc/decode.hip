@@ -504,7 +504,9 @@ __device__ __forceinline__ void down_steps(int C, int R, const ExpertPool& ep,
 // tokens runs the one-group body (batches twice as long) even if the call
 // needs two.  The waves split either every expert's k-steps (each wave a range
 // of each expert), or with FLAT the concatenated k-steps of all experts, so
-// that a wave streams long runs of one to a few experts (kDownFlatSteps).
+// that a wave streams long runs of one to a few experts (kDownFlatSteps); then
+// the waves of all gridDim.y workgroups of a row tile do, and out holds a
+// partial output per blockIdx.y.
 template <int NGMAX, int KS, bool I4, int HD, bool TE, bool FLAT>
 __global__ __launch_bounds__(64 * KS) void decode_down_kernel(
     int C, int R, int T, int max_active, ExpertPool ep, const DecodeWork* __restrict__ work,

@@ -4,8 +4,8 @@
 //   gate/up:  H'[pos][r] = sigma_r * silu(sigma_r * (Qg x)_r) * sigma_r * (Qu x)_r   (bf16)
 //   down:     Y[s][pos][c] = sum over the s-th k-chunk of r of Qd[c][r] * H'[pos][r]   (fp32)
 //   combine:  out[t] = sum_j w[t,j] * sum_s Y[s][inv[t*k+j]] + shared experts
-// A workgroup owns a tile of 512 weight rows (gate/up: 256 of each) by 128
-// tokens; its 4 waves split the weight rows, so every wave covers the same
+// A workgroup owns a tile of 512 weight rows (gate/up: 256 of each; down of
+// few tiles: 128) by 128 tokens; its 4 waves split the weight rows, so every wave covers the same
 // tokens and all of them skip the 16-token subtiles past the group's end.
 // Packed int8 tiles go to LDS as they are (a ring of three stages, loads two
 // stages ahead) and each wave widens its own 16x32 operand fragments to bf16
