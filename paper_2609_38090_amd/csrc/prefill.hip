@@ -124,10 +124,14 @@ struct Frag {
 // tied so no use of them moves above the wait.
 template <int N, int MS>
 __device__ __forceinline__ void lgkm_wait_all(Frag<MS>& f, v4i (&q)[kNarrowTiles]) {
-  asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(N));
-#pragma unroll
-  for (int ms = 0; ms < MS; ++ms) asm volatile("" : "+v"(f.bx[ms][0]), "+v"(f.bx[ms][1]));
-  asm volatile("" : "+v"(q[0]), "+v"(q[1]));
+  static_assert(MS == 8, "token subtiles of a narrow tile");
+  asm volatile("s_waitcnt lgkmcnt(%18)"
+               : "+v"(f.bx[0][0]), "+v"(f.bx[0][1]), "+v"(f.bx[1][0]), "+v"(f.bx[1][1]),
+                 "+v"(f.bx[2][0]), "+v"(f.bx[2][1]), "+v"(f.bx[3][0]), "+v"(f.bx[3][1]),
+                 "+v"(f.bx[4][0]), "+v"(f.bx[4][1]), "+v"(f.bx[5][0]), "+v"(f.bx[5][1]),
+                 "+v"(f.bx[6][0]), "+v"(f.bx[6][1]), "+v"(f.bx[7][0]), "+v"(f.bx[7][1]),
+                 "+v"(q[0]), "+v"(q[1])
+               : "i"(N));
 }
 template <int N, int MS>
 __device__ __forceinline__ void lgkm_wait_all(Frag<MS>& f, v4i (&q)[kWideTiles]) {
@@ -704,8 +708,11 @@ __device__ __forceinline__ void tile_kloop(v4f (&acc)[WT][MS], int nst, DmaFn dm
     step(s, fa, fb);
     if (s + 1 < nst) step(s + 1, fb, fa);
   }
-  // drain the trailing reads before the ring is reused
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  // drain the trailing reads before the ring is reused; their registers stay
+  // taken until here, so that nothing else is put where a read still lands
+  lgkm_wait_all<0>(fa, q);
+  lgkm_wait_all<0>(fb, q);
+  asm volatile("" ::: "memory");
   mfma_drain(acc);
 }
 
