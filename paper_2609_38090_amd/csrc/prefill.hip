@@ -29,12 +29,23 @@ static_assert(kPrefBM == 128, "the token stage holds 128 rows");
 
 // Tile shapes, by the 16-row packed tiles WT of a wave: 8 (512 weight rows
 // per workgroup tile), or 2 for a down GEMM whose 512-row tiles would leave
-// more than half of the CUs idle.
+// more than half of the CUs idle.  Where the narrow ones run: launch_prefill.
+// A narrow tile of few tokens is bound by what a CU can have delivered: it
+// loads only the token rows that it reads, and its k loop keeps to 256
+// registers (64 accumulators among them), so that a CU holds two workgroups.
+// With all 128 rows loaded and one workgroup per CU, calls of 257 to 512 narrow
+// tiles ran in two rounds and were up to 11% slower than with wide tiles (C 2304,
+// R 8192, 8 experts top-2, 32 tokens: 131 us wide, 146 then, 111 now).
 constexpr int kWideTiles = 8, kNarrowTiles = 2;
 __host__ __device__ constexpr int tile_rows(int WT) { return 4 * WT * 16; }
 constexpr int wstage_bytes(int WT) { return tile_rows(WT) * 64; }  // packed tiles per stage (WT 8: 32 KB)
 constexpr int stage_bytes(int WT) { return wstage_bytes(WT) + kXStage; }
-constexpr int dma_per_stage(int WT) { return WT + 4; }  // loads per wave and stage: tiles, then row groups
+// Groups of 8 token rows that a wave loads per stage: all 128 rows of the
+// stage, but in narrow tiles only the MS subtiles of 16 that the tile reads
+// (MS subtiles: 2, 4 or 8).
+__host__ __device__ constexpr int row_groups(int WT, int MS) { return WT == kNarrowTiles ? MS / 2 : 4; }
+// loads per wave and stage: tiles, then row groups
+constexpr int dma_per_stage(int WT, int MS) { return WT + row_groups(WT, MS); }
 static_assert(kNStage * stage_bytes(kWideTiles) <= 160 * 1024, "LDS ring exceeds 160 KB");
 
 // 16 int8 -> two groups of 8 bf16.  int8 -> fp32 is exact and an integer of
@@ -124,14 +135,27 @@ struct Frag {
 // tied so no use of them moves above the wait.
 template <int N, int MS>
 __device__ __forceinline__ void lgkm_wait_all(Frag<MS>& f, v4i (&q)[kNarrowTiles]) {
-  static_assert(MS == 8, "token subtiles of a narrow tile");
-  asm volatile("s_waitcnt lgkmcnt(%18)"
-               : "+v"(f.bx[0][0]), "+v"(f.bx[0][1]), "+v"(f.bx[1][0]), "+v"(f.bx[1][1]),
-                 "+v"(f.bx[2][0]), "+v"(f.bx[2][1]), "+v"(f.bx[3][0]), "+v"(f.bx[3][1]),
-                 "+v"(f.bx[4][0]), "+v"(f.bx[4][1]), "+v"(f.bx[5][0]), "+v"(f.bx[5][1]),
-                 "+v"(f.bx[6][0]), "+v"(f.bx[6][1]), "+v"(f.bx[7][0]), "+v"(f.bx[7][1]),
-                 "+v"(q[0]), "+v"(q[1])
-               : "i"(N));
+  if constexpr (MS == 8) {
+    asm volatile("s_waitcnt lgkmcnt(%18)"
+                 : "+v"(f.bx[0][0]), "+v"(f.bx[0][1]), "+v"(f.bx[1][0]), "+v"(f.bx[1][1]),
+                   "+v"(f.bx[2][0]), "+v"(f.bx[2][1]), "+v"(f.bx[3][0]), "+v"(f.bx[3][1]),
+                   "+v"(f.bx[4][0]), "+v"(f.bx[4][1]), "+v"(f.bx[5][0]), "+v"(f.bx[5][1]),
+                   "+v"(f.bx[6][0]), "+v"(f.bx[6][1]), "+v"(f.bx[7][0]), "+v"(f.bx[7][1]),
+                   "+v"(q[0]), "+v"(q[1])
+                 : "i"(N));
+  } else if constexpr (MS == 4) {
+    asm volatile("s_waitcnt lgkmcnt(%10)"
+                 : "+v"(f.bx[0][0]), "+v"(f.bx[0][1]), "+v"(f.bx[1][0]), "+v"(f.bx[1][1]),
+                   "+v"(f.bx[2][0]), "+v"(f.bx[2][1]), "+v"(f.bx[3][0]), "+v"(f.bx[3][1]),
+                   "+v"(q[0]), "+v"(q[1])
+                 : "i"(N));
+  } else {
+    static_assert(MS == 2, "token subtiles per tile: 8, 4 or 2");
+    asm volatile("s_waitcnt lgkmcnt(%6)"
+                 : "+v"(f.bx[0][0]), "+v"(f.bx[0][1]), "+v"(f.bx[1][0]), "+v"(f.bx[1][1]),
+                   "+v"(q[0]), "+v"(q[1])
+                 : "i"(N));
+  }
 }
 template <int N, int MS>
 __device__ __forceinline__ void lgkm_wait_all(Frag<MS>& f, v4i (&q)[kWideTiles]) {
@@ -592,6 +616,17 @@ __device__ __forceinline__ void mfma_drain(v4f (&acc)[8][2]) {
                  "+a"(acc[6][0]), "+a"(acc[6][1]), "+a"(acc[7][0]), "+a"(acc[7][1]));
 }
 
+__device__ __forceinline__ void mfma_drain(v4f (&acc)[kNarrowTiles][2]) {
+  asm volatile("s_nop 7\n s_nop 7\n s_nop 7\n"
+               : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[1][0]), "+a"(acc[1][1]));
+}
+
+__device__ __forceinline__ void mfma_drain(v4f (&acc)[kNarrowTiles][4]) {
+  asm volatile("s_nop 7\n s_nop 7\n s_nop 7\n"
+               : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
+                 "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]));
+}
+
 __device__ __forceinline__ void mfma_drain(v4f (&acc)[kNarrowTiles][8]) {
   asm volatile("s_nop 7\n s_nop 7\n s_nop 7\n"
                : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
@@ -634,15 +669,17 @@ __device__ __forceinline__ void stage_body(v4f (&acc)[WT][MS], const Frag<MS>& c
     q[J] = lds_read128<wtile_off<DUAL>(J)>(a.w);
     static_for<b0, b1>([&](auto i) { read_bx<WT, MS, i>(nxt, a); });
     v4i nlo, nhi;
-    if constexpr (WT == kNarrowTiles) {
-      dma16(dma(3 * J));
-      const Dma d[2] = {dma(3 * J + 1), dma(3 * J + 2)};
-      mfma_chunk(acc[J], cur, lo, hi, qn, nlo, nhi, d);
-    } else if constexpr (J < 4) {
-      const Dma d[2] = {dma(2 * J), dma(2 * J + 1)};
+    // loads of this chunk: D0 .. D1-1, the last one or two inside it
+    constexpr int D0 = WT == kNarrowTiles ? (J * dma_per_stage(WT, MS) + 1) / 2 : J < 4 ? 2 * J : 4 + J;
+    constexpr int D1 = WT == kNarrowTiles ? ((J + 1) * dma_per_stage(WT, MS) + 1) / 2
+                                          : J < 4 ? 2 * J + 2 : 5 + J;
+    static_assert(D1 - D0 >= 1 && D1 - D0 <= 3, "loads per chunk");
+    if constexpr (D1 - D0 == 3) dma16(dma(D0));
+    if constexpr (D1 - D0 >= 2) {
+      const Dma d[2] = {dma(D1 - 2), dma(D1 - 1)};
       mfma_chunk(acc[J], cur, lo, hi, qn, nlo, nhi, d);
     } else {
-      const Dma d[1] = {dma(4 + J)};
+      const Dma d[1] = {dma(D0)};
       mfma_chunk(acc[J], cur, lo, hi, qn, nlo, nhi, d);
     }
     lo = nlo;
@@ -653,11 +690,11 @@ __device__ __forceinline__ void stage_body(v4f (&acc)[WT][MS], const Frag<MS>& c
 }
 
 // Wait until at most n whole stages of this wave's loads are in flight.
-template <int WT>
+template <int WT, int MS>
 __device__ __forceinline__ void wait_stages(int n) {
-  static_assert(kNStage <= 4 && dma_per_stage(WT) * (kNStage - 1) < 64, "vmcnt immediates");
-  if (n >= 2) wait_vmcnt<2 * dma_per_stage(WT)>();
-  else if (n == 1) wait_vmcnt<dma_per_stage(WT)>();
+  static_assert(kNStage <= 4 && dma_per_stage(WT, MS) * (kNStage - 1) < 64, "vmcnt immediates");
+  if (n >= 2) wait_vmcnt<2 * dma_per_stage(WT, MS)>();
+  else if (n == 1) wait_vmcnt<dma_per_stage(WT, MS)>();
   else wait_vmcnt<0>();
 }
 
@@ -674,8 +711,8 @@ __device__ __forceinline__ void tile_kloop(v4f (&acc)[WT][MS], int nst, DmaFn dm
 
   const int pre = nst < kNStage ? nst : kNStage;
   for (int s = 0; s < pre; ++s)
-    for (int i = 0; i < dma_per_stage(WT); ++i) dma16(dma(s, i));
-  wait_stages<WT>(pre - 1);
+    for (int i = 0; i < dma_per_stage(WT, MS); ++i) dma16(dma(s, i));
+  wait_stages<WT, MS>(pre - 1);
   ring_barrier();  // stage 0 is in LDS for every wave
 
   Frag<MS> fa, fb;
@@ -695,7 +732,7 @@ __device__ __forceinline__ void tile_kloop(v4f (&acc)[WT][MS], int nst, DmaFn dm
   int slot_next = 1 % kNStage;
   auto step = [&](int s, Frag<MS>& cur, Frag<MS>& nxt) {
     lgkm_wait_all<0>(cur, q);
-    wait_stages<WT>(pre - 2);  // one refill per step: stage s+1 has pre-2 refills behind it
+    wait_stages<WT, MS>(pre - 2);  // one refill per step: stage s+1 has pre-2 refills behind it
     ring_barrier();
     // past the end of the tile the slot is reloaded with its own stage s (a
     // harmless copy), which keeps one code path and a fixed queue depth
@@ -795,10 +832,9 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     const int32_t* __restrict__ tokpos, const uint16_t* __restrict__ act,
     const uint16_t* __restrict__ act_lo, uint16_t* __restrict__ hout,
     uint16_t* __restrict__ hout_lo, float* __restrict__ yout, size_t ysplit) {
-  // LDS ring of three 48 KB slots: 32 packed tiles exactly as in HBM (1 KB
-  // each), then 128 token rows x 64 bf16 with the 16-byte chunk c of row r at
-  // chunk c ^ ((r >> 1) & 7): the 64 banks span two 128-byte rows, so the 16
-  // rows of one read phase land on 16 distinct 16-byte bank groups.
+  // LDS ring of three slots: 4 * WT packed tiles exactly as in HBM (1 KB each),
+  // then 128 token rows x 64 bf16 with the 16-byte chunk c of row r at chunk
+  // c ^ tok_swizzle(r): 48 KB a slot in wide tiles, 24 KB in narrow ones.
   __shared__ __attribute__((aligned(1024))) int8_t ring[kNStage * stage_bytes(WT)];
 
   const int K = DUAL ? C : R;   // contraction length
@@ -820,10 +856,8 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     const uint32_t o = (uint32_t)b * stage_bytes(WT);
     return StageAddr{wl + o, xl0 + o, xl1 + o};
   };
-  // LDS destinations of this wave's loads: packed tiles 8w..8w+7 and token
-  // rows 32w..32w+31 of a slot
+  // LDS destination of this wave's packed tiles WT*w .. WT*w + WT-1 of a slot
   const uint32_t m0_w = ring_base + wave * WT * 1024;
-  const uint32_t m0_x = ring_base + wstage_bytes(WT) + wave * 32 * 128;
 
   // group tables in LDS (offsets, slots and the prefix of m-tiles of kPrefBM
   // positions over groups); the tile walk below reads them for every tile
@@ -878,10 +912,15 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
   const int ks_per = (nks + KS - 1) / KS;
   const int per_m = NT * KS;  // tiles per m-tile
   const int total = n_mt * per_m;
+  // A narrow grid holds two workgroups per CU, so the calls it serves often
+  // have fewer tiles than workgroups: only as many as there are tiles work,
+  // or the runs below would load some XCDs twice and leave others idle.
+  const int nw = WT == kNarrowTiles ? min(nb, (total + 7) & ~7) : nb;
+  if (WT == kNarrowTiles && (int)blockIdx.x >= nw) return;
 
   // XCD-aware order: workgroups b, b+8, b+16, ... share an XCD, so give each
   // XCD a contiguous run of logical tiles
-  const int bid = (nb % 8 == 0) ? (blockIdx.x % 8) * (nb / 8) + blockIdx.x / 8 : blockIdx.x;
+  const int bid = (nw % 8 == 0) ? (blockIdx.x % 8) * (nw / 8) + blockIdx.x / 8 : blockIdx.x;
 
   // tile tau -> (group, m-tile, k-chunk, n-tile): groups in order, m-tiles
   // fastest so the m-tiles sharing a weight tile run side by side
@@ -901,21 +940,28 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     const int p0 = s_off[g] + ml * kPrefBM;
     return Tile{g, p0, min(kPrefBM, s_off[g + 1] - p0), rest % KS, (rest / KS) * rows_per_mat};
   };
-  // token rows of this wave's four DMA row groups: rows past the group read
+  // token subtiles of a tile's body (the group's last tile runs a shorter one
+  // when it holds at most 64 or 32 tokens) and this wave's first token row
+  auto subtiles = [&](int nv) { return nv > 64 ? 8 : nv > 32 ? 4 : 2; };
+  auto first_row = [&](int nv) { return wave * 8 * row_groups(WT, subtiles(nv)); };
+  // token rows of this wave's DMA row groups: rows past the group read
   // its first row instead (their products are never stored)
   auto src_rows = [&](const Tile& t, int (&rows)[4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int r = wave * 32 + i * 8 + (lane >> 3);
+      const int r = first_row(t.nv) + i * 8 + (lane >> 3);
       const int pr = t.p0 + (r < t.nv ? r : 0);
       rows[i] = DUAL ? tokpos[pr] : pr;
     }
   };
 
   int rows[4] = {0, 0, 0, 0};
-  if (bid < total) src_rows(describe(bid), rows);
-  for (int tau = bid; tau < total; tau += nb) {
+  if (WT == kWideTiles && bid < total) src_rows(describe(bid), rows);
+  for (int tau = bid; tau < total; tau += nw) {
     const Tile t = describe(tau);
+    // narrow down tiles: the rows are plain positions, and four registers fewer
+    // in the k loop are what lets a CU hold two workgroups
+    if constexpr (WT == kNarrowTiles) src_rows(t, rows);
     const int g = t.g, p0 = t.p0, nv = t.nv, n0 = t.n0;
     const int ks0 = t.split * ks_per, ks1 = min(nks, ks0 + ks_per);
     const int nst = ks1 - ks0;
@@ -926,8 +972,8 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     const int8_t* blob = ep.pool + (size_t)(ok ? slot_id : 0) * ep.stride;
     const int8_t* wbase = blob + (DUAL ? 0 : (size_t)2 * R * C);
 
-    // Sources of this wave's direct-to-LDS loads: packed tiles 8w..8w+7 and
-    // 4 groups of 8 token rows per stage, as 32-bit lane offsets from a
+    // Sources of this wave's direct-to-LDS loads: its WT packed tiles and its
+    // groups of 8 token rows per stage, as 32-bit lane offsets from a
     // scalar base that advances by one stage.  Rows past the matrix read a
     // valid row instead (their products are never stored).
     uint32_t woff[WT], xoff[4];
@@ -941,12 +987,12 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int r = wave * 32 + i * 8 + (lane >> 3);
+      const int r = first_row(nv) + i * 8 + (lane >> 3);
       const int c = (lane & 7) ^ tok_swizzle(r);
       xoff[i] = (uint32_t)(((size_t)rows[i] * K + c * 8) * 2);
     }
     // the next tile's token rows load while this tile computes
-    if (tau + nb < total) src_rows(describe(tau + nb), rows);
+    if (WT == kWideTiles && tau + nw < total) src_rows(describe(tau + nw), rows);
     if (!ok) {
       // A missing expert contributes nothing: its partial outputs are zero,
       // so the combine (which sums every position's partials) leaves its term
@@ -963,7 +1009,8 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
     const int8_t* wstage0 = wbase + (size_t)ks0 * 1024;
     const int8_t* xstage0 = (const int8_t*)(act + (size_t)ks0 * 64);
     const int8_t* xstage0_lo = act_lo ? (const int8_t*)(act_lo + (size_t)ks0 * 64) : xstage0;
-    // load i of stage s: packed tiles for i < 8, token row groups after;
+    const uint32_t m0_x = ring_base + wstage_bytes(WT) + first_row(nv) * 128;
+    // load i of stage s: packed tiles for i < WT, token row groups after;
     // stages nst .. 2*nst-1 (two-pass calls) repeat the weights over act_lo
     auto dma = [&](int s, int i) {
       const uint32_t so = (uint32_t)(s % kNStage) * stage_bytes(WT);
@@ -988,16 +1035,9 @@ __global__ __launch_bounds__(kGemmThreads) void prefill_gemm_kernel(
       tile_kloop<DUAL, WT, MS>(acc, nst_all, dma, slot);
       tile_epilogue<DUAL, WT, MS>(acc, wave, lane, n0, N, R, C, p0, nv, blob, hout, hout_lo, ybase);
     };
-    // token subtiles actually present: the group's last tile runs a shorter
-    // loop when it holds at most 64 or 32 tokens (a narrow tile's stage has 32
-    // MFMAs and waits for its loads either way)
-    if constexpr (WT == kNarrowTiles) {
-      run(std::integral_constant<int, 8>{});
-    } else {
-      if (nv > 64) run(std::integral_constant<int, 8>{});
-      else if (nv > 32) run(std::integral_constant<int, 4>{});
-      else run(std::integral_constant<int, 2>{});
-    }
+    if (nv > 64) run(std::integral_constant<int, 8>{});
+    else if (nv > 32) run(std::integral_constant<int, 4>{});
+    else run(std::integral_constant<int, 2>{});
   }
 }
 
@@ -1087,9 +1127,12 @@ hipError_t launch_prefill(const mira_shape& s, const Layout& L, const WsPtr& w, 
   // Down in tiles of 512 rows, or of 128 where even the upper bound of 512-row
   // tiles (k-chunks included) would leave more than half of the CUs without
   // one: a narrow tile's token stages are read by four times the workgroups,
-  // but the chain of stages runs four times as wide.  301 fp32 tokens, C 1024,
-  // R 2816, 16 + 1 experts (about 40 wide tiles): the layer call took 195 us
-  // with wide tiles and takes 132 us.
+  // but the chain of stages runs four times as wide.  Over 145 such calls (17 to
+  // 1200 tokens, bf16 and fp32, C 512 to 5120, R 512 to 12288, 4 to 48 experts, 36
+  // to 150 wide tiles) the layer call is 1.05 to 1.6 times as fast: 301 fp32
+  // tokens, C 1024, R 2816, 16 + 1 experts 195 us wide, 131 narrow; C 768, R 5312,
+  // 400 fp32 tokens 311 / 202; C 2304, R 5312, 17 experts top-5, 43 tokens 188 /
+  // 163; C 5120, R 512, 200 fp32 tokens 190 / 182.
   const auto down = [&](auto wt) {
     constexpr int WT = wt;
     auto kern = prefill_gemm_kernel<false, WT>;

@@ -32,6 +32,19 @@ CASES = [
 ]
 
 
+# The body and the token rows that a tile loads go by its token count: 32, 64 and
+# 128 tokens are the last of each (one expert holds every token; 129 leave a
+# second tile of one).
+CASES += [(f"tokens_{t}", _cfg(770 + i, t, 192, 320, 1, 1)) for i, t in enumerate((32, 33, 64, 65, 128, 129))]
+CASES += [
+    ("tokens_48_f32", _cfg(780, 48, 320, 128, 1, 1, act="f32")),
+    # more narrow tiles than CUs (18 row tiles of 17 experts), and more workgroups
+    # than tiles (most experts without a token)
+    ("two_per_cu", _cfg(781, 43, 2304, 128, 17, 5)),
+    ("few_of_many", _cfg(782, 17, 128, 64, 120, 1)),
+]
+
+
 @pytest.mark.parametrize("cfg", [pytest.param(c, id=i) for i, c in CASES])
 def test_narrow_down(mira, cfg):
     run_and_check(Layer(cfg))
