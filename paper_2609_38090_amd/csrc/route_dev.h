@@ -22,41 +22,39 @@ constexpr int kBigWaves = kBigThreads / 64;
 // accumulate, the k range split over the waves.
 // ---------------------------------------------------------------------------
 // fp32 logits of nt <= 16 tokens from row x on, experts e_begin .. e_end-1, by
-// a workgroup of nwaves waves: a wave takes 4 tokens x 4 experts at a time and
-// reads their rows with 16-byte loads, so that a router row serves four tokens
-// and a wave has up to 20 loads in flight (one token and expert at a time, with
-// 4-byte loads, this was bound by load latency: 301 tokens x 16 experts x 1024
-// took 106 us).  A logit's sum does not depend on the tile it is computed in:
-// lane l adds columns 256 i + 4 l + j in the order of (i, j), then the lanes add.
-__device__ __forceinline__ void logits_f32(const float* __restrict__ x,
-                                           const float* __restrict__ wr,
-                                           const float* __restrict__ bias, int nt, int C,
-                                           int e_begin, int e_end, int nwaves,
-                                           float (*lg)[MIRA_MAX_EXPERTS]) {
+// a workgroup of nwaves waves: a wave takes Q tokens x Q experts at a time and
+// reads their rows with 16-byte loads, B chunks of 256 columns in flight.  A
+// logit's sum does not depend on Q, B or the tile it is computed in: lane l
+// adds columns 256 i + 4 l + j in the order of (i, j), then the lanes add.
+template <int Q, int B>
+__device__ __forceinline__ void logits_f32_tiles(const float* __restrict__ x,
+                                                 const float* __restrict__ wr,
+                                                 const float* __restrict__ bias, int nt, int C,
+                                                 int e_begin, int e_end, int nwaves,
+                                                 float (*lg)[MIRA_MAX_EXPERTS]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nq = (nt + 3) / 4, ne = (e_end - e_begin + 3) / 4;
-  constexpr int B = 2;  // 256-column chunks in flight
+  const int nq = (nt + Q - 1) / Q, ne = (e_end - e_begin + Q - 1) / Q;
   for (int it = wave; it < nq * ne; it += nwaves) {
-    const int t0 = (it % nq) * 4, e0 = e_begin + (it / nq) * 4;
-    const float *xr[4], *wrow[4];
+    const int t0 = (it % nq) * Q, e0 = e_begin + (it / nq) * Q;
+    const float *xr[Q], *wrow[Q];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < Q; ++j) {
       xr[j] = x + (size_t)min(t0 + j, nt - 1) * C + lane * 4;
       wrow[j] = wr + (size_t)min(e0 + j, e_end - 1) * C + lane * 4;
     }
-    float acc[4][4];
+    float acc[Q][Q];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < Q; ++t)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[t][e] = 0.f;
+      for (int e = 0; e < Q; ++e) acc[t][e] = 0.f;
     for (int c0 = 0; c0 < C; c0 += 256 * B) {
-      v4f xv[B][4], wv[B][4];
+      v4f xv[B][Q], wv[B][Q];
 #pragma unroll
       for (int b = 0; b < B; ++b) {
         const int c = c0 + 256 * b;
         const bool in = c + lane * 4 < C;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < Q; ++j) {
           xv[b][j] = in ? *(const v4f*)(xr[j] + c) : v4f{0.f, 0.f, 0.f, 0.f};
           wv[b][j] = in ? *(const v4f*)(wrow[j] + c) : v4f{0.f, 0.f, 0.f, 0.f};
         }
@@ -64,21 +62,39 @@ __device__ __forceinline__ void logits_f32(const float* __restrict__ x,
 #pragma unroll
       for (int b = 0; b < B; ++b)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < Q; ++t)
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
+          for (int e = 0; e < Q; ++e)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[t][e] = fmaf(xv[b][t][j], wv[b][e][j], acc[t][e]);
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < Q; ++t)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < Q; ++e) {
         const float s = wave_sum(acc[t][e]);
         if (lane == 0 && t0 + t < nt && e0 + e < e_end)
           lg[t0 + t][e0 + e] = s + (bias ? bias[e0 + e] : 0.f);
       }
   }
+}
+
+// Tiles of 4 x 4, where a router row serves four tokens and a wave has 16
+// loads in flight (one token and expert at a time, with 4-byte loads, this was
+// bound by load latency: 301 tokens x 16 experts x 1024 took 106 us).  Where
+// every token and expert can have a wave of its own, single ones: 4 x 4 tiles
+// leave most waves idle there (us per layer call, 4 x 4 / single: 4 tokens, 4
+// experts, C 512 19.3 / 16.8; 2 tokens, 8 experts, C 2048 25.8 / 21.3; 1 token, 16
+// experts, C 1024 19.0 / 16.4; C 6144, 8 experts, 33.9 / 26.6).
+__device__ __forceinline__ void logits_f32(const float* __restrict__ x,
+                                           const float* __restrict__ wr,
+                                           const float* __restrict__ bias, int nt, int C,
+                                           int e_begin, int e_end, int nwaves,
+                                           float (*lg)[MIRA_MAX_EXPERTS]) {
+  if (nt * (e_end - e_begin) <= nwaves)
+    logits_f32_tiles<1, 4>(x, wr, bias, nt, C, e_begin, e_end, nwaves, lg);
+  else
+    logits_f32_tiles<4, 2>(x, wr, bias, nt, C, e_begin, e_end, nwaves, lg);
 }
 
 // Workgroup barrier for LDS traffic only: global loads still in flight (the

@@ -90,6 +90,12 @@ ROUTE = [
     ("many", _cfg(744, 16, 512, 64, 100, 8), 0),
     ("f32", _cfg(745, 7, 1088, 64, 30, 3, act="f32"), 0),
     ("f32_one_launch", _cfg(746, 5, 320, 64, 7, 3, act="f32"), 0),
+    # fp32 with a wave per token and expert (at most 16) and the next call in 4 x 4
+    # tiles; columns past the last whole pass of either
+    ("f32_single", _cfg(757, 4, 576, 64, 4, 2, act="f32"), 0),
+    ("f32_single_one", _cfg(758, 1, 1088, 64, 16, 3, act="f32"), 0),
+    ("f32_tiles", _cfg(759, 3, 1088, 64, 6, 2, act="f32"), 0),
+    ("f32_split_one", _cfg(760, 1, 2112, 64, 29, 3, act="f32"), 0),
     # fp32 columns past the last whole pass, ragged token and expert quads
     ("f32_prefill", _cfg(747, 37, 576, 64, 21, 4, act="f32"), 0),
     # one token: rank counting (E < 2k) and repeated maxima, at their border
