@@ -143,12 +143,13 @@ __device__ __forceinline__ void decode_gateup_groups(int C, int R, const ExpertP
     decode_gateup_body<NGMAX, NGMAX, HD, I4, false>(C, R, rb, slot, ep, wk, xdig, hdig, hexp, bmax);
 }
 
-template <int NGMAX, bool I4>
-__global__ __launch_bounds__(256) void decode_gateup_kernel(int C, int R, ExpertPool ep,
-                                                            DecodeWork* __restrict__ work,
-                                                            const int8_t* __restrict__ xdig,
-                                                            int8_t* __restrict__ hdig,
-                                                            int32_t* __restrict__ hexp) {
+// WG workgroups per CU (waves per SIMD) at least.
+template <int NGMAX, bool I4, int WG>
+__global__ __launch_bounds__(256, WG) void decode_gateup_kernel(int C, int R, ExpertPool ep,
+                                                                DecodeWork* __restrict__ work,
+                                                                const int8_t* __restrict__ xdig,
+                                                                int8_t* __restrict__ hdig,
+                                                                int32_t* __restrict__ hexp) {
   decode_gateup_groups<NGMAX, I4, false>(C, R, ep, work, xdig, hdig, hexp);
 }
 
@@ -647,6 +648,18 @@ static void launch_decode_down_ng(const Layout& L, const WsPtr& w, const ExpertP
                decode_max_active(L), ep, w.dwork, w.hdig, w.hexp, out);
 }
 
+// Largest hidden size for which the INT8 gate/up kernels of two and three token
+// groups keep three workgroups on a CU.  The bodies by token count take a few
+// registers more than the 168 that allow it.  Up to 1024 (16 k-steps) a
+// workgroup is over after two weight batches, and a third one hides the start
+// of the next; with longer rows two workgroups of looser schedule are even or
+// ahead.  us per call with two / three: C 512, R 8192, 8 experts top-2, 8 tokens
+// 56.4 / 54.9; C 768, R 13952, 8 experts top-5 and one shared, 8 tokens 141.7 /
+// 138.1; C 1024, R 4096, 16 experts top-4 and one shared, 6 tokens 44.1 / 41.5; C
+// 1536, R 2048, 13 tokens 53.7 / 55.4; C 2048, R 1408, 64 experts top-6, 2 shared,
+// 15 tokens 72.1 / 74.9; Mixtral shape, 8 tokens 215.9 / 216.7.
+constexpr int kThreePerCuMaxC = 1024;
+
 template <int NG, bool I4>
 static void launch_decode_gateup(const Layout& L, const WsPtr& w, const ExpertPool& ep,
                                  hipStream_t st) {
@@ -660,8 +673,12 @@ static void launch_decode_gateup(const Layout& L, const WsPtr& w, const ExpertPo
       return;
     }
   }
-  launch_timed("decode_gateup", (decode_gateup_kernel<NG, I4>), dim3(max_active * nrb),
-               dim3(256), 0, st, L.C, L.R, ep, w.dwork, w.xdig, w.hdig, w.hexp);
+  auto kern = decode_gateup_kernel<NG, I4, 1>;
+  if constexpr (!I4 && (NG == 2 || NG == 3)) {
+    if (L.C <= kThreePerCuMaxC) kern = decode_gateup_kernel<NG, I4, 3>;
+  }
+  launch_timed("decode_gateup", kern, dim3(max_active * nrb), dim3(256), 0, st, L.C, L.R, ep,
+               w.dwork, w.xdig, w.hdig, w.hexp);
 }
 
 // One token: the 16-row tiles of all active experts split evenly over the

@@ -66,6 +66,11 @@ GATEUP = [
     ("t11", _cfg(722, 11, 192, 192, 6, 2, S=1), "int8"),
     ("t15", _cfg(723, 15, 192, 192, 12, 4, S=1), "int8"),
     ("t16", _cfg(724, 16, 192, 192, 12, 4, S=1), "int8"),
+    # the largest hidden size with three workgroups per CU and the next one
+    ("three_per_cu", _cfg(730, 8, 1024, 192, 12, 4, S=1), "int8"),
+    ("three_per_cu_3", _cfg(731, 13, 1024, 128, 12, 4, S=1, act="f32"), "int8"),
+    ("two_per_cu", _cfg(732, 8, 1088, 192, 12, 4, S=1), "int8"),
+    ("two_per_cu_3", _cfg(733, 13, 1088, 128, 12, 4, S=1), "int8"),
     ("t10_int4", _cfg(725, 10, 256, 128, 24, 3, S=1), "int4"),
     ("t16_int4", _cfg(726, 16, 384, 256, 12, 4, S=1), "int4"),
     ("t6_int4_f32", _cfg(727, 6, 128, 128, 12, 2, act="f32"), "int4"),

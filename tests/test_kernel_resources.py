@@ -58,6 +58,10 @@ def test_no_vector_spills(kernels):
 @pytest.mark.parametrize("part,most", [
     # narrow prefill down tiles: two workgroups of four waves per CU
     ("prefill_gemm_kernelILb0ELi2E", 256),
+    # INT8 gate/up of two and three token groups at small hidden sizes: three
+    # workgroups of four waves per CU
+    ("decode_gateup_kernelILi2ELb0ELi3E", 168),
+    ("decode_gateup_kernelILi3ELb0ELi3E", 168),
 ])
 def test_occupancy(kernels, part, most):
     assert _vgprs(kernels, part) <= most
