@@ -490,7 +490,8 @@ __device__ inline void permute_decode_wave(const int32_t* idx, const float* wts,
     if (o.order_out) o.order_out[pos] = Tk + i;
   }
   __builtin_amdgcn_wave_barrier();
-  // non-empty groups, most tokens first -> descriptors (headers by the owning
+  // non-empty groups, most tokens first (more than 64 pairs: at least five tokens)
+  // -> descriptors (headers by the owning
   // lane, then the per-position fields spread over all lanes)
   const int n_active = __shfl(ia, 63, 64);
   int a4[4] = {0, 0, 0, 0}, run_a = 0;
@@ -568,12 +569,19 @@ __device__ __forceinline__ void pair_masks(bool ok, int e, int E, uint64_t& eq, 
 }
 
 // DecodeWork descriptors and the residency status of a call with T*k <= 64
-// pairs (one wave): what the expert kernels read, the groups of most tokens
-// first.  (A gate/up workgroup of more tokens runs longer, and in expert order
-// the largest groups could start last: 8 / 16 tokens, us per call in expert
-// order and in this one: Mixtral shape INT8 188.3 / 254.4 -> 182.5 / 244.0, INT4
-// 141.6 / 200.1 -> 137.2 / 187.7; fine-grained INT4 51.8 / 83.1 -> 50.0 / 75.0.)  Positions i >= n of a
-// descriptor are left as they were (the kernels read only i < n).
+// pairs (one wave): what the expert kernels read.  Up to one token group (5
+// tokens) every gate/up workgroup runs the same body, and the groups stay in
+// expert order, the shared experts last: an order by size only cost (C 768, R
+// 13952, 8 experts top-5, 5 tokens 126.4 -> 128.7 us per call; C 1024, R 8192, 2
+// tokens 56.2 -> 56.7; the fine-grained layer, 2 and 4 tokens, 0.3 to 0.6 us).
+// Above that the groups of most tokens come first, for a workgroup of more
+// tokens runs longer and in expert order the largest groups could start last:
+// fine-grained layer with uniform routing, 6 / 8 / 10 tokens, us per call in
+// expert order and in this one: INT8 61.7 / 74.1 / 81.2 -> 59.2 / 70.1 / 77.8,
+// INT4 52.6 / 63.8 / 71.2 -> 51.3 / 58.8 / 65.2; Mixtral shape, 16 tokens, 255.5
+// -> 250.2; with skewed routing, and at 8 to 12 tokens of Mixtral's shape, the
+// two are within 2% of each other either way.  Positions i >= n of a descriptor
+// are left as they were (the kernels read only i < n).
 __device__ inline void decode_work_small(const int32_t* idx_s, const float* w_s, const int* xe_s,
                                          const int* slot_s, int T, int k, int E, int S,
                                          const ExpertPool& ep, DecodeWork* __restrict__ work,
@@ -590,16 +598,23 @@ __device__ inline void decode_work_small(const int32_t* idx_s, const float* w_s,
   const bool lead = ok && rank == 0;
   const int n = __popcll(eq);
   const int nr = __popcll(__ballot(lead));
-  // descriptors: shared experts (every token), then the routed groups, most
-  // tokens first; a group's lanes take its leader's index
-  int a = 0, run_a = S;
-  uint32_t sizes = wave_or_u32(ok ? 1u << n : 0u);  // bit v: some group has v tokens
-  while (sizes) {
-    const int v = 31 - __builtin_clz(sizes);
-    sizes ^= 1u << v;
-    const uint64_t mask = __ballot(lead && n == v);
-    if (ok && n == v) a = run_a + __popcll(mask & ((eq & (0 - eq)) - 1));
-    run_a += __popcll(mask);
+  // descriptor a of this lane's group, sh of the first shared expert
+  int a = 0, sh = 0;
+  if (T <= kTokPerGroup) {
+    a = __popcll(lo & __ballot(lead));
+    sh = nr;
+  } else {
+    // shared experts (every token), then the routed groups, most tokens first;
+    // a group's lanes take its leader's index
+    int run_a = S;
+    uint32_t sizes = wave_or_u32(ok ? 1u << n : 0u);  // bit v: some group has v tokens
+    while (sizes) {
+      const int v = 31 - __builtin_clz(sizes);
+      sizes ^= 1u << v;
+      const uint64_t mask = __ballot(lead && n == v);
+      if (ok && n == v) a = run_a + __popcll(mask & ((eq & (0 - eq)) - 1));
+      run_a += __popcll(mask);
+    }
   }
   int bits = 0;
   if (lead) {
@@ -622,7 +637,7 @@ __device__ inline void decode_work_small(const int32_t* idx_s, const float* w_s,
   for (int s = lane; s < S; s += 64) {
     const int slot = slot_s[E + s];
     bits |= slot < 0 ? 1 : (slot >= ep.n_slots ? 2 : 0);
-    DecodeWork* wk = work + s;
+    DecodeWork* wk = work + sh + s;
     wk->group = E + s;
     wk->slot = slot;
     wk->off = P + s * T;
@@ -630,7 +645,7 @@ __device__ inline void decode_work_small(const int32_t* idx_s, const float* w_s,
   }
   for (int i = lane; i < S * T; i += 64) {
     const int s = i / T, t = i - s * T;
-    DecodeWork* wk = work + s;
+    DecodeWork* wk = work + sh + s;
     wk->tok[t] = t;
     wk->xe[t] = xe_s[t];
     wk->w[t] = 1.0f;

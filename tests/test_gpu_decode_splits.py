@@ -110,6 +110,9 @@ ROUTE = [
     # every group size up to T, in both descriptor forms; equal sizes
     ("sizes", _cfg(753, 16, 128, 64, 20, 3, S=2), 0),
     ("sizes_many", _cfg(754, 16, 128, 64, 40, 8, S=2), 0),
+    # expert order up to five tokens, sizes above; shared experts at either end
+    ("order_5", _cfg(734, 5, 128, 64, 12, 4, S=3), 0),
+    ("order_6", _cfg(735, 6, 128, 64, 12, 4, S=3), 0),
     ("sizes_equal", _cfg(755, 16, 128, 64, 8, 8, S=3), 0),
     ("sizes_254", _cfg(756, 16, 64, 64, 250, 16, S=4), 0),
     ("one_all", _cfg(751, 1, 128, 64, 9, 2, S=1, act="f32"), 1),
