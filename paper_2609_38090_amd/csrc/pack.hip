@@ -386,8 +386,12 @@ __global__ __launch_bounds__(256) void pack_quant_wide_kernel(
 
 // INT4 from bf16: a wave per (matrix, tile row, run of column pairs), two
 // groups of 64 columns at a time, the group maxima over the four lanes of a
-// row.  Two Mixtral experts 246 -> 202 us; from fp32 one thread per group
-// (pack_i4_kernel) already reads at the copy rate and is 5% ahead.
+// row.  For large experts (i4_wide).  A wave has one pair's loads in flight, so
+// it takes many waves, in short runs of even length: with runs of up to 1 / 2 / 4 /
+// 8 pairs, two Mixtral experts take 215 / 204 / 200 / 202 us, three of 4096 x 4096
+// 95.4 / 92.4 / 92.8 / 95.5, four of 4096 x 4096 - / 120 / 120 / 122.
+constexpr int kPackI4Run = 2;
+
 __global__ __launch_bounds__(256) void pack_i4_wide_kernel(const uint16_t* __restrict__ wg,
                                                            const uint16_t* __restrict__ wu,
                                                            const uint16_t* __restrict__ wd, int C,
@@ -397,14 +401,14 @@ __global__ __launch_bounds__(256) void pack_i4_wide_kernel(const uint16_t* __res
   const int mat = blockIdx.y, e = blockIdx.z;
   const int rows = mat == 2 ? C : R, K = mat == 2 ? R : C;
   const int lane = threadIdx.x & 63, r16 = lane & 15, kg = lane >> 4;
-  const int npair = K / 128, runs = (npair + kPackUnitTiles / 2 - 1) / (kPackUnitTiles / 2);
+  const int npair = K / 128, runs = (npair + kPackI4Run - 1) / kPackI4Run;
   const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int rt = unit / runs, p0 = (unit % runs) * (kPackUnitTiles / 2);
+  const int rt = unit / runs, part = unit % runs;
   if (rt >= rows / 16) return;
   const uint16_t* src = (mat == 0 ? wg : mat == 1 ? wu : wd) + (size_t)e * R * C +
                         (size_t)(rt * 16 + r16) * K + kg * 16;
   uint8_t* m = packed + (size_t)e * stride + (size_t)mat * i4_matrix_bytes(R, C);
-  const int p1 = min(npair, p0 + kPackUnitTiles / 2);
+  const int p0 = part * npair / runs, p1 = (part + 1) * npair / runs;
   for (int p = p0; p < p1; ++p) {
     W16<uint16_t> w[2];
     w[0].load(src + p * 128);
@@ -434,6 +438,25 @@ static bool wide_ok(int C, int R, const void* wg, const void* wu, const void* wd
   return C % 64 == 0 && R % 64 == 0 && ((uintptr_t)wg | (uintptr_t)wu | (uintptr_t)wd) % 16 == 0;
 }
 
+// Whether n INT4 experts from bf16 take whole tiles (pack_i4_wide_kernel) and not
+// a thread per group (pack_i4_kernel).  The latter writes a packed tile from 16
+// rows that are C/64 (gate, up) threads apart, so it loses with long rows; whole
+// tiles need enough of them to fill the chip.  us, a thread per group / whole
+// tiles, of n experts C x R:
+//   4096 x 4096: n 1 35.5 / 36.8, 2 66.5 / 64.5, 3 98.2 / 92.3
+//   2560 x 6144: n 1 32.8 / 35.1, 2 62.2 / 61.2, 3 91 / 87    2688 x 1152, 13: 75.9 / 78.3
+//   2048 x 8320, 6: 188 / 181    2048 x 2048, 17: 118 / 127    8192 x 2048, 2: 70.1 / 64.4
+//   2944 x 1280, 14: 98.9 / 98.5    2048 x 1408, 60: 286 / 315    512 x 15232, 18: 248 / 245
+// Over 90 random shapes (C 512 to 8192, R 256 to 16384, 4 * 10^7 to 4.5 * 10^8
+// weights) no call that the rule sends to whole tiles was slower for it, the
+// largest 1.35 times as fast; of the others some would gain (4736 x 896, 27
+// experts: 223 / 208).  From fp32 a thread per group already reads at the copy
+// rate and is 5% ahead.
+static bool i4_wide(int C, int R, int n) {
+  const double per = (double)C * R, all = 3 * per * n;
+  return per >= 5e6 && all >= 7e7 && all * C >= 4.1e11;
+}
+
 template <typename WT>
 static void launch_pack_wide(int C, int R, int n, const WT* wg, const WT* wu, const WT* wd, float eps,
                              int8_t* packed, uint64_t stride, uint32_t* amax, hipStream_t st) {
@@ -456,11 +479,10 @@ hipError_t launch_pack_i4(int C, int R, int n, int w_dtype, const void* wg, cons
   prof_begin("pack", st);
   const int64_t items = (int64_t)R * (C / 64);  // rows x groups, the same for all three matrices
   const dim3 grid((unsigned)((items + 255) / 256), 3, n);
-  if (w_dtype == MIRA_BF16 && wide_ok(C, R, wg, wu, wd)) {
+  if (w_dtype == MIRA_BF16 && i4_wide(C, R, n) && wide_ok(C, R, wg, wu, wd)) {
     // tile rows x runs of column pairs, the larger of gate's and down's
     const auto waves = [](int rows, int K) {
-      constexpr int run = kPackUnitTiles / 2;
-      return (int64_t)(rows / 16) * ((K / 128 + run - 1) / run);
+      return (int64_t)(rows / 16) * ((K / 128 + kPackI4Run - 1) / kPackI4Run);
     };
     const int64_t units = waves(R, C) > waves(C, R) ? waves(R, C) : waves(C, R);
     hipLaunchKernelGGL(pack_i4_wide_kernel, dim3((unsigned)((units + 3) / 4), 3, n), dim3(256), 0, st,

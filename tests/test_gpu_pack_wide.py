@@ -21,6 +21,11 @@ CASES = [  # hidden, ffn, experts, dtype, magnitude, int4
     (384, 1152, 2, "bf16", 1e-7, True),
     (256, 256, 1, "bf16", 1e8, True),
     (256, 384, 1, "f32", 1.0, True),
+    # INT4 from bf16 takes whole tiles for large experts only: runs of one and two
+    # column pairs in both dimensions, runs of two, and one expert too few
+    (6016, 896, 5, "bf16", 0.02, True),
+    (5888, 1024, 4, "bf16", 1e-7, True),
+    (6016, 896, 4, "bf16", 0.02, True),
 ]
 
 
