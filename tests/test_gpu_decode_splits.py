@@ -16,7 +16,8 @@ selects inside the gate/up kernel.  Descriptors are ordered by token count."""
 import numpy as np
 import pytest
 
-from gpu_layer import Layer, decode_rel_floor, run_and_check
+import oracle
+from gpu_layer import Layer, LazyBlobs, assert_ffn_close, decode_rel_floor, run_and_check
 from mira_inputs import MoEConfig
 
 pytestmark = pytest.mark.gpu
@@ -132,8 +133,37 @@ def test_route_split(mira, cfg, softmax_all):
         assert np.array_equal(v, two[name]), name
     if not softmax_all:
         run_and_check(lay, res=res)
-    else:  # the oracle's helper checks renormalised weights; these sum to less
-        lg = res["logits"].astype(np.float64)
-        p = np.exp(lg - lg.max(1, keepdims=True))
-        p /= p.sum(1, keepdims=True)
-        assert np.allclose(res["w"], np.take_along_axis(p, res["idx"].astype(np.int64), 1), rtol=0, atol=2e-6)
+        return
+    # the oracle's helper checks renormalised weights; these sum to less.  The
+    # selection is the sort of the logits, and weights and output are the oracle's
+    # under it
+    x, wr, b = lay.oracle_inputs()
+    lg = res["logits"].astype(np.float64)
+    assert np.max(np.abs(lg - oracle.router_logits(x, wr, b)) / np.maximum(1.0, np.abs(lg))) < 2e-5
+    for t in range(cfg.T):
+        assert res["idx"][t].tolist() == sorted(range(cfg.E), key=lambda e: (-lg[t, e], e))[:cfg.k], t
+    ref = oracle.moe_forward(x, wr, b, LazyBlobs(lay), cfg.k, cfg.C, cfg.R, shared_blobs=lay.shared_blobs(),
+                             norm_topk=False, idx=res["idx"])
+    assert np.max(np.abs(res["w"] - ref["w"])) < 2e-5
+    assert_ffn_close(res["out"], ref["out"], cfg.name)
+
+
+@pytest.mark.parametrize("softmax_all", [0, 1])
+@pytest.mark.parametrize("cfg", [
+    # rank counting (E < 2k) and repeated maxima, shared experts, the most experts
+    pytest.param(_cfg(783, 1, 256, 256, 12, 7, S=2), id="counting"),
+    pytest.param(_cfg(784, 1, 384, 384, 64, 6, S=3), id="maxima"),
+    pytest.param(_cfg(785, 1, 4096, 128, 8, 2), id="lds_last"),
+    pytest.param(_cfg(786, 1, 128, 256, 9, 2, S=1, act="f32"), id="f32"),
+])
+def test_one_token_int4_selection(mira, cfg, softmax_all):
+    """A one-token INT4 call, which selects inside gate/up, against the two-phase
+    call (a selection kernel) bit for bit, and against the oracle."""
+    lay = Layer(cfg, fmt="int4")
+    flags = mira.MIRA_FLAG_SOFTMAX_ALL if softmax_all else 0
+    res = lay.run(flags, ws_fill=0xFF)
+    two = lay.run(flags, two_phase=True, ws_fill=0xFF)
+    for name, v in res.items():
+        assert np.array_equal(v, two[name]), name
+    if not softmax_all:
+        run_and_check(lay, res=res)
