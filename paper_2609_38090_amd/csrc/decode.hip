@@ -36,7 +36,10 @@ inline uint32_t xl_bytes(int C) { return 3 * kTokPerGroup * (C + 16); }
 // Mixtral shape 2%)
 constexpr int kXlUnroll = 8;
 // the same for an INT8 expert of one token group in a call of several: the
-// body shares its registers with the wider ones
+// body shares its registers with the wider ones.  us per call with 4 / 8 / 16
+// steps: Mixtral shape, 13 tokens 242.0 / 238.0 / 237.4; fine-grained layer, 9
+// tokens 59.3 / 57.9 / 57.4; but 16 steps do not fit three workgroups per CU
+// (kThreePerCuMaxC), where they spill: C 1024, R 4096, 6 tokens 41.5 / 41.6 / 61.9
 constexpr int kOneGroupUnroll = 8;
 // k-steps per weight batch of the one-token INT4 tile kernel (6 KB per wave):
 // a wave holds one tile and cannot issue its next loads while it unpacks and
@@ -99,8 +102,8 @@ __device__ __forceinline__ void decode_gateup_body(int C, int R, int rb, int slo
                                                    (const uint8_t*)ep.pool + (size_t)slot * ep.stride,
                                                    wk.off, bv, xev, load_b, hdig, hexp, bmax);
   else
-    gateup_block<NG, HD, (NGMAX > 1 && NG == 1) ? kOneGroupUnroll : dec_unroll(NG)>(C, R, rb, ep.pool + (size_t)slot * ep.stride, wk.off, bv, xev, load_b, hdig,
-                         hexp, bmax);
+    gateup_block<NG, HD, (NGMAX > 1 && NG == 1) ? kOneGroupUnroll : dec_unroll(NG)>(
+        C, R, rb, ep.pool + (size_t)slot * ep.stride, wk.off, bv, xev, load_b, hdig, hexp, bmax);
 }
 
 // Workgroup = (non-empty expert, 64-row block) of a call that NGMAX token
@@ -353,11 +356,13 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void decode_gateup_tile_i4_kern
 }
 
 // ---------------------------------------------------------------------------
-// Down projection + weighted combine.  Workgroup = 16 output rows c; its KS
-// waves split the k-steps (64 entries of R each) of the non-empty experts.
+// Down projection + weighted combine.  Workgroup = 16 output rows c, or an
+// equal part of their k-steps (64 entries of R each): the KS waves of the one to
+// four workgroups of a row tile split the k-steps of the non-empty experts.
 // For every expert, y = Qd H' with per-64-row exponents of H', multiplied by
 // the combine weight of each (token, expert) pair and summed per token in a
-// fixed order (expert list order inside a wave, then wave order), so the
+// fixed order (expert list order inside a wave, then wave order, then the
+// partial outputs of the workgroups in order, by decode_add_kernel), so the
 // result is deterministic.  H' has HD digits per entry (h_digits): an operand
 // of 16 columns holds 5 tokens of three digits or 8 of two (column r16 = token
 // r16/HD of the group, digit r16%HD), and NG groups cover that many tokens.
@@ -581,6 +586,7 @@ __global__ __launch_bounds__(64 * KS) void decode_down_kernel(
 }
 
 // out = sum over p < parts of part[p], in order; n floats each, n a multiple of 4
+// (out is 16-byte aligned, as every entry point requires)
 __global__ __launch_bounds__(256) void decode_add_kernel(const float* __restrict__ part, int parts,
                                                          float* __restrict__ out, int n) {
   const int i = (blockIdx.x * 256 + threadIdx.x) * 4;
@@ -621,8 +627,8 @@ constexpr int kDownFlatSteps = 96;
 // 512, R 2816, 64 experts top-4: 2 tokens 30.6 / 29.0 / - , 8 tokens 43.0 /
 // 38.0 / 33.8, 16 tokens 66.3 / 56.9 / 49.6.  Below 300 steps it is even.
 constexpr int kDownPartSteps = 150, kDownMaxParts = 4;
-static int down_parts(const Layout& L, const float* out) {
-  if (L.T == 1 || L.R / 64 > kDownFlatSteps || (uintptr_t)out % 16 != 0) return 1;
+static int down_parts(const Layout& L) {
+  if (L.T == 1 || L.R / 64 > kDownFlatSteps) return 1;
   int parts = std::min(kDownMaxParts, device_cu_count() / (L.C / 16));
   parts = std::min(parts, decode_max_active(L) * (L.R / 64) / kDownPartSteps);
   parts = std::min(parts, L.ksplit * L.P / L.T);
@@ -633,7 +639,7 @@ template <int NG, bool I4, int HD, bool TE = false>
 static void launch_decode_down_ng(const Layout& L, const WsPtr& w, const ExpertPool& ep,
                                   float* out, hipStream_t st) {
   constexpr int KS = down_waves<I4>();
-  const int parts = down_parts(L, out);
+  const int parts = down_parts(L);
   if (parts > 1) {
     launch_timed("decode_down", (decode_down_kernel<NG, KS, I4, HD, TE, true>), dim3(L.C / 16, parts),
                  dim3(64 * KS), 0, st, L.C, L.R, L.T, decode_max_active(L), ep, w.dwork, w.hdig, w.hexp, w.ybuf);

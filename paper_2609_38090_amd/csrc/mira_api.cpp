@@ -140,7 +140,8 @@ mira::ExpertPool pool_of(const mira_moe_args* a) {
 int run_route(const mira_shape* s, const mira_moe_args* a, const mira::Layout& L, hipStream_t st) {
   mira::WsPtr w = mira::ws_ptrs(L, a->workspace);
   if (use_decode(*s, L.T)) {
-    // one workgroup: router, top-k, permutation and the digits of x
+    // router, top-k, permutation and the digits of x, in one launch or (large
+    // routers) two
     HIP_TRY(mira::launch_decode_prep(*s, L, w, a->x, a->w_router, a->router_bias, a->logits,
                                      pool_of(a), a->expert_counts, a->topk_idx, a->topk_weight,
                                      a->expert_offsets, a->pair_order, st));

@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void pack_i4_kernel(const WT* __restrict__ wg,
 // element per thread with byte stores took 830 us.  Cutting the work into
 // rounds of 48 to 192 MB, whose second read would come from the Infinity Cache,
 // was slower (421 to 579 us).  The narrow kernels above take what is left:
-// odd sizes and unaligned weights.
+// odd sizes and unaligned weights, and most INT4 calls (i4_wide).
 // ---------------------------------------------------------------------------
 // 16 consecutive weights of one lane as fp32 values.
 template <typename WT>
@@ -316,8 +316,9 @@ __global__ __launch_bounds__(256) void pack_max_wide_kernel(const WT* __restrict
   }
 }
 
-// Quantizes expert blockIdx.y, one wave per unit: 16 column blocks of one tile row of gate or up (which also writes the
-// rows' sigma), or 16 tile rows of one column block of down.
+// Quantizes expert blockIdx.y, one wave per unit: 16 column blocks of one tile row
+// of gate or up (which also writes the rows' sigma), or 16 tile rows of one column
+// block of down.
 constexpr int kPackUnitTiles = 16;
 
 template <typename WT>

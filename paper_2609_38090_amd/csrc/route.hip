@@ -688,7 +688,11 @@ static void launch_logits(const mira_shape& s, const Layout& L, const WsPtr& w, 
 // us per layer call in one launch / in two, one launch costing about 2 us more
 // than none: 70 KB (17 experts of C = 1024) 17.4 / 20.9 with one token, 96 KB
 // 35.0 / 34.8 with 4 tokens and 62.2 / 60.8 with 16, 160 KB 88.9 / 85.3 with
-// 16, 256 KB 55.3 / 49.8 with 4 and 102 / 93 with 16.
+// 16, 256 KB 55.3 / 49.8 with 4 and 102 / 93 with 16.  fp32 (vector units, so the
+// tokens count for more): with 16 tokens two are ahead from 40 KB on (31.6 / 29.1),
+// with 5 from about 100 KB (640 x 40 26.3 / 21.7, 1024 x 32 23.9 / 23.1, 2048 x 20
+// even), with 2 from about 280 KB (1024 x 32 20.0 / 20.8, 4096 x 18 34.6 / 34.5); the
+// same line lies between.
 constexpr size_t kSplitRouterBytes = 96 << 10;
 
 hipError_t launch_decode_prep(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,

@@ -1,7 +1,8 @@
 // Device-side routing helpers of the routing kernels: router logits for up
-// to 16 tokens, top-k by rank counting with the combine weights, and the
-// one-wave stable grouping of a decode call's (token, slot) pairs (paper section II-A: the router scores every
-// expert, the top-k experts process the token, their outputs are combined).
+// to 16 tokens, top-k (rank counting or repeated maxima) with the combine
+// weights, and the one-wave stable grouping of a decode call's (token, slot)
+// pairs (paper section II-A: the router scores every expert, the top-k experts
+// process the token, their outputs are combined).
 #pragma once
 
 #include "device_util.h"
@@ -490,9 +491,9 @@ __device__ inline void permute_decode_wave(const int32_t* idx, const float* wts,
     if (o.order_out) o.order_out[pos] = Tk + i;
   }
   __builtin_amdgcn_wave_barrier();
-  // non-empty groups, most tokens first (more than 64 pairs: at least five tokens)
-  // -> descriptors (headers by the owning
-  // lane, then the per-position fields spread over all lanes)
+  // non-empty groups, most tokens first (more than 64 pairs: at least five
+  // tokens) -> descriptors (headers by the owning lane, then the per-position
+  // fields spread over all lanes)
   const int n_active = __shfl(ia, 63, 64);
   int a4[4] = {0, 0, 0, 0}, run_a = 0;
   uint32_t sizes = 0;  // bit v: some group has v tokens
