@@ -742,8 +742,22 @@ hipError_t launch_decode(const mira_shape& s, const Layout& L, const WsPtr& w, c
   return hipGetLastError();
 }
 
+// Tiles per CU up to which a call of at most 16 experts selects inside gate/up.
+// Eight waves fill a CU, and every further round of workgroups selects anew
+// before it streams, where a router of one expert tile costs the preparation
+// kernel little.  us per call, selection inside / in the preparation kernel: 8
+// tiles per CU (16 experts top-8, R 4096), C 512 64.6 / 65.6 (two layers), C 4096
+// 77.6 / 78.1; 12 (10 experts top-4, 2 shared), C 768, R 8192 99.3 / 99.4 (two);
+// 16 (16 experts top-8, R 8192), C 768 121.2 / 120.4 (two), C 2048 90.1 / 90.0; 22, C
+// 512, R 11456 148.6 / 145.2 (two); 28, C 1024, R 14336 109.2 / 106.2, INT4 85.8 /
+// 83.6.  With more experts the preparation kernel costs more, and selecting inside
+// is ahead at any count (64 experts top-6, 2 shared, C 512, R 11456, 22 tiles: 73.5 /
+// 76.3).
+constexpr int kFusedTilesPerCu = 12;
+
 bool one_token_fused(const mira_shape& s, const Layout& L) {
-  return L.T == 1 && L.E <= 64 && L.k + L.S <= 64 && (!(s.flags & MIRA_FLAG_INT4) || L.C <= kXlMaxC);
+  return L.T == 1 && L.E <= 64 && L.k + L.S <= 64 && (!(s.flags & MIRA_FLAG_INT4) || L.C <= kXlMaxC) &&
+         (L.E > 16 || decode_max_active(L) * (L.R / 16) <= kFusedTilesPerCu * device_cu_count());
 }
 
 hipError_t launch_one_token(const mira_shape& s, const Layout& L, const WsPtr& w, const void* x,

@@ -12,7 +12,8 @@ digits of one-group experts in LDS up to hidden 4096.
 
 Routing: large routers (more than 16 experts and 96 KB of rows) compute their
 logits in a launch of their own; a whole one-token call with at most 64 experts
-selects inside the gate/up kernel.  Descriptors are ordered by token count."""
+selects inside the gate/up kernel (up to 16 experts: if its tiles are few).
+Descriptors are ordered by token count, up to five tokens by expert."""
 import numpy as np
 import pytest
 
@@ -116,6 +117,10 @@ ROUTE = [
     ("order_6", _cfg(735, 6, 128, 64, 12, 4, S=3), 0),
     ("sizes_equal", _cfg(755, 16, 128, 64, 8, 8, S=3), 0),
     ("sizes_254", _cfg(756, 16, 64, 64, 250, 16, S=4), 0),
+    # the most tiles (12 per CU) of a call of 16 experts that selects inside
+    # gate/up, and the next one
+    ("one_tiles_last", _cfg(736, 1, 64, 6144, 16, 8), 0),
+    ("one_tiles_next", _cfg(737, 1, 64, 6208, 16, 8), 0),
     ("one_all", _cfg(751, 1, 128, 64, 9, 2, S=1, act="f32"), 1),
     ("three_all", _cfg(752, 3, 128, 64, 40, 5), 1),
 ]
