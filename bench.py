@@ -54,17 +54,17 @@ PROF_EVERY = 8  # steps timed with events: one layer-copy rotation in every 8
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 TRAFFIC = {
     ("decode_gateup", "mixtral_decode"): dict(sources=("decode.hip", "decode_dev.h", "int4_format.h"),
-                                               sha="2b2b8f93748da802", fetch_kib=114834.8, write_kib=110.3),
+                                               sha="bb748e4d0fee22eb", fetch_kib=114849.3, write_kib=110.5),
     ("decode_gateup", "mixtral_decode_int4"): dict(sources=("decode.hip", "decode_dev.h", "int4_format.h"),
-                                                    sha="2b2b8f93748da802", fetch_kib=61622.0, write_kib=110.1),
+                                                    sha="bb748e4d0fee22eb", fetch_kib=61643.8, write_kib=110.2),
     # the beam stack's decode_gateup: the mean over all its launches (32
     # layers, 5.38 selected experts per layer on average)
     ("decode_gateup", "beam_stack"): dict(sources=("decode.hip", "decode_dev.h", "int4_format.h"),
-                                          sha="2b2b8f93748da802", fetch_kib=308765.0, write_kib=560.3),
-    ("prefill_gateup", "mixtral_prefill"): dict(sources=("prefill.hip",), sha="8d87e7443ab4d714",
-                                                 fetch_kib=600413.4, write_kib=38203.4),
-    ("prefill_gateup", "fine_grained"): dict(sources=("prefill.hip",), sha="8d87e7443ab4d714",
-                                              fetch_kib=290638.8, write_kib=57853.3),
+                                          sha="bb748e4d0fee22eb", fetch_kib=308789.3, write_kib=560.4),
+    ("prefill_gateup", "mixtral_prefill"): dict(sources=("prefill.hip",), sha="a93d33db9b497625",
+                                                 fetch_kib=599060.3, write_kib=38686.0),
+    ("prefill_gateup", "fine_grained"): dict(sources=("prefill.hip",), sha="a93d33db9b497625",
+                                              fetch_kib=290212.3, write_kib=57924.3),
 }
 
 
