@@ -124,7 +124,7 @@ __device__ __forceinline__ void dma16(const Dma& d) {
 
 // Token fragments of one 64-wide k stage held by one wave: MS subtiles of
 // 16 tokens, two 128-bit reads per lane (k 16kg..16kg+7 and 16kg+8..16kg+15
-// of token row r16).  The wave's eight packed weight tiles of the stage are
+// of token row r16).  The wave's WT packed weight tiles of the stage are
 // read one by one into a rolling set of registers.
 template <int MS>
 struct Frag {
@@ -219,7 +219,7 @@ struct StageAddr {
 
 // LDS offset of the wave's j-th weight tile from its first one.  DUAL: gate
 // tiles 4w..4w+3 then up tiles 16+4w..16+4w+3 (so acc[j] and acc[j+4] are
-// the gate and up rows of the same H' columns); otherwise tiles 8w..8w+7.
+// the gate and up rows of the same H' columns); otherwise tiles WT*w .. WT*w+WT-1.
 template <bool DUAL>
 __device__ __forceinline__ constexpr int wtile_off(int j) {
   return DUAL ? (j < 4 ? j : 12 + j) * 1024 : j * 1024;
@@ -645,8 +645,8 @@ __device__ __forceinline__ void read_bx(Frag<MS>& f, const StageAddr& a) {
   else f.bx[I >> 1][0] = lds_read128<wstage_bytes(WT) + (I >> 1) * 2048>(a.x0);
 }
 
-// One stage.  On entry: cur holds this stage's token fragments, q[1..7] this
-// stage's weight tiles 1..7 and c0lo/c0hi its widened tile 0.  Chunk j runs
+// One stage.  On entry: cur holds this stage's token fragments, q[1..WT-1] this
+// stage's weight tiles 1..WT-1 and c0lo/c0hi its widened tile 0.  Chunk j runs
 // the MFMAs of tile j, widens tile j+1, reads the next stage's weight tile j
 // into q[j] (free since its widening in chunk j-1) and a share of its token
 // fragments into nxt, and issues a share of the refill dma(j, i).  On exit
